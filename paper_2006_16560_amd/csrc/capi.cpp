@@ -75,6 +75,7 @@ struct petar_ctx {
 
     int force_waves[2][5] = {{0}};
     int nb_waves = 0;
+    int cus = 0;
 
     // captured step (petar_step_graph)
     hipStream_t cap_stream = nullptr;
@@ -895,14 +896,15 @@ petar_status alloc_force(petar_ctx *ctx, const ForceArgs &a) {
     const int prec = ctx->params.precision, ipl = ctx->params.i_per_lane;
     int &fw = ctx->force_waves[prec][ipl];
     if (fw == 0) fw = force_resident_waves(prec, ipl, ctx->device);
+    if (ctx->cus == 0) ctx->cus = force_cus(ctx->device);
     if (a.nb && ctx->nb_waves == 0) ctx->nb_waves = nb_resident_waves(ctx->device);
-    int spill_waves = fw > ctx->nb_waves ? fw : ctx->nb_waves;
+    const int spill_waves = std::max({fw, ctx->nb_waves, force_team_walkers(ctx->device)});
     TRY(ensure(ctx, ctx->rr, (size_t)n * sizeof(double2)));
     TRY(ensure(ctx, ctx->rsk, (size_t)n * 8));
     TRY(ensure(ctx, ctx->gflag, (size_t)(n_nodes + 1) * 4));
     TRY(ensure(ctx, ctx->gpos, (size_t)(n_nodes + 1) * 4));
     TRY(ensure(ctx, ctx->groups, (size_t)n_nodes * 4));
-    TRY(ensure(ctx, ctx->queue, 64 * 4));
+    TRY(ensure(ctx, ctx->queue, kQueueWords * 4));
     TRY(ensure(ctx, ctx->spill, (size_t)spill_waves * (size_t)kSpillCap * 4));
     if (ctx->params.record_counts) TRY(ensure(ctx, ctx->counts, (size_t)n * 4 * 4));
     if (a.nb) {
@@ -953,7 +955,7 @@ void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbR
     NbRecords rec;
     rec.head = ptr<uint4>(ctx->nbhead);
     rec.leaf = ptr<uint2>(ctx->nbleaf);
-    rec.count = queue + 16;  // [16] headers, [17] leaf entries (zeroed with the queue)
+    rec.count = queue + kQueueRec;  // headers, leaf entries (zeroed with the queue)
     rec.head_cap = ctx->nbhead_cap;
     rec.leaf_cap = ctx->nbleaf_cap;
     const uint32_t *groups = ptr<uint32_t>(ctx->groups);
@@ -978,7 +980,7 @@ void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbR
     scan_u32_to_i64(cnt, nb->offsets_dev, n, ws, s);
     launch_nb_sort(row_off, rows, nb->offsets_dev, nb->idx_dev, n, nb->capacity, st, cnt,
                    queue + 10, s);
-    launch_nb_summary(nb->offsets_dev, row_off, n, queue + 16, st, s);
+    launch_nb_summary(nb->offsets_dev, row_off, n, queue + kQueueRec, st, s);
     if (timed) (void)hipEventRecord(ctx->ev[7], s);
 }
 
@@ -994,7 +996,7 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     uint32_t *queue = ptr<uint32_t>(ctx->queue);
     if (timed) (void)hipEventRecord(ctx->ev[2], s);
     zero_force_status(ctx, s);
-    fill_u32(queue, 0, 64, s);
+    fill_u32(queue, 0, kQueueWords, s);
     launch_gather_radii(a.r_in, a.r_out, a.r_search, t, st, s);
     launch_rsmax(t, s);
     launch_group_flags(pre, t, a.group_size, ptr<uint32_t>(ctx->gflag), s);
@@ -1023,11 +1025,11 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     f.acc = a.acc;
     f.pot = a.pot;
     f.spill = ptr<uint32_t>(ctx->spill);
-    f.queue = queue;
+    f.queue = queue + kQueueForce;
     f.counts = ctx->params.record_counts ? ptr<int32_t>(ctx->counts) : nullptr;
     f.nb.head = a.nb ? ptr<uint4>(ctx->nbhead) : nullptr;
     f.nb.leaf = a.nb ? ptr<uint2>(ctx->nbleaf) : nullptr;
-    f.nb.count = queue + 16;  // [16] headers, [17] leaf entries (zeroed with the queue)
+    f.nb.count = queue + kQueueRec;  // headers, leaf entries (zeroed with the queue)
     f.nb.head_cap = a.nb ? ctx->nbhead_cap : 0;
     f.nb.leaf_cap = a.nb ? ctx->nbleaf_cap : 0;
     f.nb_bound = a.nb ? ptr<uint32_t>(ctx->nbcnt) : nullptr;
@@ -1037,6 +1039,8 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     f.tidx = tidx;
     f.precision = prec;
     f.ipl = ipl;
+    f.group_size = a.group_size;
+    f.cus = ctx->cus;
     if (timed) (void)hipEventRecord(ctx->ev[4], s);
     launch_force(f, fw, s);
     if (timed) (void)hipEventRecord(ctx->ev[5], s);

@@ -120,6 +120,14 @@ struct NbRecords {
     uint32_t head_cap, leaf_cap;
 };
 
+// Words of the context's queue buffer: the neighbour passes' queues and
+// counters first, then the near-leaf claims, then the force kernel's heads;
+// the claimed words lie in cache lines of their own.
+constexpr int kQueueStride = 32;               // 128 B
+constexpr int kQueueRec = kQueueStride;        // [0] headers, [1] leaf entries
+constexpr int kQueueForce = 2 * kQueueStride;  // 8 heads, kQueueStride words apart
+constexpr int kQueueWords = 10 * kQueueStride;
+
 struct ForceLaunch {
     TreeDev t;
     const uint32_t *groups;
@@ -129,7 +137,7 @@ struct ForceLaunch {
     double G;
     double *acc, *pot;         // caller's outputs, input order
     uint32_t *spill;           // walk stack spill, per resident wave
-    uint32_t *queue;           // 8 work-queue heads
+    uint32_t *queue;           // 8 work-queue heads, kQueueStride words apart
     int32_t *counts;           // optional per-particle counts [4][n]
     NbRecords nb;              // near-leaf lists for the neighbour passes (head null: none)
     uint32_t *nb_bound;        // optional [n], input order: particles of the group's near
@@ -138,6 +146,8 @@ struct ForceLaunch {
     double kick_dt;
     int precision;             // 0 mixed, 1 fp64
     int ipl;                   // 1, 2, 4
+    int group_size;            // of the walk; with n, the number of groups to expect
+    int cus;                   // compute units of the device
     // optional target subset: tpos[k] = targets before Morton position k
     // ([n + 1]), tidx = their Morton positions; null: every particle
     const uint32_t *tpos, *tidx;
@@ -151,6 +161,9 @@ void launch_target_compact(const uint32_t *flag, const uint32_t *tpos, int64_t n
                            hipStream_t s);
 int force_resident_waves(int precision, int ipl, int device);
 int64_t force_spill_elems_per_wave();
+// Walkers with a spill area when the groups are run by teams of waves.
+int force_team_walkers(int device);
+int force_cus(int device);
 void launch_force(const ForceLaunch &f, int resident_waves, hipStream_t s);
 
 // -------------------------------------------------------------- nblist.hip

@@ -1452,3 +1452,43 @@ def test_back_to_back_builds_growing(pt, orc):
     pt.petar_tree_build(c2, T(small.pos), T(small.mass), 0.5, 8)
     st2 = pt.petar_get_stats(c2)  # counters of a build not followed by a force call
     assert st2["n"] == 3000 and st2["n_leaves"] > 0 and st2["ms_build"] > 0.0
+
+
+# ---------------------------------------------------- groups run by teams
+@pytest.mark.parametrize("n,group,leaf", [
+    (6463, 64, 8), (6464, 64, 8),    # teams of 16 and 8 (n / group = 100, 101)
+    (1401, 2, 4), (1402, 2, 4),      # teams of 8 and 4 (700, 701)
+    (20000, 1, 8), (20001, 1, 8),    # teams of 4, one wave (20000, 20001)
+    (701, 1, 300), (3000, 300, 150),  # groups of more than 64 targets in chunks
+])
+def test_force_by_teams(pt, ctx, orc, n, group, leaf):
+    """At the sizes where the team per group changes: FP64 against the oracle
+    tree (1e-12, counts equal), lists bit-exact; mixed with two targets per
+    lane (teams) bitwise equal to four (one wave per group; the same sum order
+    for groups of up to 128 targets, above them the chunks of 128 and 256 split
+    the last targets' sources differently), and on a subset with massless sources, FP64 within 1e-12 of the oracle."""
+    c, rin, rout, rs = cluster_with_radii(orc, n, n, bf=0.3)
+    acc, pot, (offs, idx), cnt = run(pt, ctx, c.pos, c.mass, rin, rout, rs, 0.5, leaf, group,
+                                     pt.PETAR_FP64, nb_cap=256 * n, counts=True)
+    a_ref, p_ref, cnt_ref = orc.tree_force(c.pos, c.mass, rin, rout, rs, 0.5, leaf, group)
+    same = np.all(cnt == cnt_ref, axis=0)
+    assert same.mean() > 0.999
+    assert rel_err(acc, a_ref)[same].max() < 1e-12
+    np.testing.assert_allclose(pot[same], p_ref[same], rtol=1e-12)
+    o_ref, i_ref = orc.neighbours(c.pos, rs)
+    assert np.array_equal(offs, o_ref) and np.array_equal(idx, i_ref)
+    two = run(pt, ctx, c.pos, c.mass, rin, rout, rs, 0.5, leaf, group, pt.PETAR_MIXED, ipl=2)
+    four = run(pt, ctx, c.pos, c.mass, rin, rout, rs, 0.5, leaf, group, pt.PETAR_MIXED, ipl=4)
+    one_chunk = cnt[3] <= 128
+    assert np.array_equal(two[0][:, one_chunk], four[0][:, one_chunk])
+    assert np.array_equal(two[1][one_chunk], four[1][one_chunk])
+    rng = np.random.default_rng(n)
+    mass = np.where(rng.random(n) < 0.3, 0.0, c.mass)
+    target = rng.random(n) < 0.5
+    pt.petar_set_params(ctx, precision=pt.PETAR_FP64, i_per_lane=2, record_counts=0)
+    pt.petar_tree_build(ctx, T(c.pos), T(mass), 0.0, leaf)
+    pt.petar_set_targets(ctx, T(target.astype(np.uint8)))
+    sub = pt.petar_force_long(ctx, group, T(rin), T(rout), T(rs))[0].cpu().numpy()
+    a_dir, _ = orc.force_long(c.pos, mass, rin, rout, idx=np.nonzero(target)[0])
+    assert rel_err(sub[:, target], a_dir).max() < 1e-12
+    assert not sub[:, ~target].any()
