@@ -50,8 +50,8 @@ struct petar_ctx {
     DevBuf nbrowoff, nbrows;  // neighbour rows: offsets (input order) and scratch
     DevBuf tflag, tpos, tidx;  // target compaction (petar_set_targets)
     // second-stage filter and clusters
-    DevBuf cl_keep, cl_row, cl_counts, cl_parent, cl_root, cl_rootpos, cl_status, cl_flags,
-        cl_key0, cl_key1, cl_val0, cl_val1;
+    DevBuf cl_masks, cl_rec, cl_counts, cl_parent, cl_root, cl_rootpos, cl_status, cl_flags,
+        cl_key0, cl_key1, cl_val0;
     // artificial particles
     DevBuf art_single, art_spos, art_status, art_pairof, tt_ginv, grp_off, grp_idx;
     bool tt_ginv_ready = false;
@@ -59,7 +59,8 @@ struct petar_ctx {
     int64_t nbrows_cap = 0;  // entries of nbrows; grown when a call's rows needed more
 
     Status *host_status = nullptr;  // pinned
-    int64_t *host_scalar = nullptr; // pinned
+    int64_t *host_scalar = nullptr; // pinned; kernels write it through scalar_dev
+    int64_t *scalar_dev = nullptr;
 
     bool have_tree = false;
     bool have_counts = false;
@@ -148,6 +149,12 @@ petar_status ensure(petar_ctx *ctx, DevBuf &b, size_t bytes) {
     b.cap = want;
     ctx->ws_bytes += (int64_t)want;
     return PETAR_OK;
+}
+
+// Whether ensure(b, bytes) would stay below the workspace cap.
+bool room_for(petar_ctx *ctx, const DevBuf &b, size_t bytes) {
+    return b.cap >= bytes || ctx->params.workspace_cap <= 0 ||
+           ctx->ws_bytes - (int64_t)b.cap + (int64_t)bytes <= ctx->params.workspace_cap;
 }
 
 template <typename T>
@@ -240,9 +247,9 @@ void free_all(petar_ctx *c) {
                       &c->gflag,    &c->gpos,        &c->groups,     &c->spill,
                       &c->queue,    &c->counts,      &c->nbcnt,      &c->radii_ws,   &c->nbhead, &c->nbleaf,
                       &c->nbrowoff, &c->nbrows,
-                      &c->cl_keep,  &c->cl_row,      &c->cl_counts,   &c->cl_parent,  &c->cl_root,    &c->cl_rootpos,
+                      &c->cl_masks, &c->cl_rec,      &c->cl_counts,   &c->cl_parent,  &c->cl_root,    &c->cl_rootpos,
                       &c->cl_status,   &c->cl_flags,   &c->cl_key0,    &c->cl_key1,
-                      &c->cl_val0,  &c->cl_val1,
+                      &c->cl_val0,
                       &c->art_single, &c->art_spos, &c->art_status, &c->art_pairof, &c->tt_ginv,
                       &c->grp_off,  &c->grp_idx,  &c->tflag,      &c->tpos,       &c->tidx,
                       &c->sys_off};
@@ -298,6 +305,7 @@ petar_status petar_create(petar_ctx **out, int device, void *hip_stream) {
         hipError_t e = hipSetDevice(device);
         if (e == hipSuccess) e = hipHostMalloc((void **)&c->host_status, sizeof(Status));
         if (e == hipSuccess) e = hipHostMalloc((void **)&c->host_scalar, kHostScalarWords * sizeof(int64_t));
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->scalar_dev, c->host_scalar, 0);
         for (int k = 0; k < 8 && e == hipSuccess; k++) e = hipEventCreate(&c->ev[k]);
         // set-up of this device's fixed scratch (petar_clusters_noalloc)
         void *scratch_ptr = nullptr;
@@ -367,48 +375,69 @@ petar_status petar_changeover_radii(petar_ctx *ctx, const double *mass, const do
 namespace {
 
 // Filter of a candidate CSR (mode 0: pericentre, mode 1: group relation) into
-// out_offsets[n + 1] / out_idx[capacity]; *required = kept entries.
+// out_offsets[n + 1] / out_idx[capacity]; *required = kept entries. With
+// out_idx null the entries go to grp_idx. One host read when the scratch of
+// an earlier call is large enough; else the passes run again with the counts
+// they gave.
 petar_status filter_impl(petar_ctx *ctx, FilterArgs a, int64_t *out_offsets, int32_t *out_idx,
                          int64_t capacity, int64_t *required) {
     const int64_t n = a.n;
     hipStream_t s = ctx->stream;
-    // candidate count and CSR sanity (one host read)
+    const bool own = out_idx == nullptr;
     TRY(ensure(ctx, ctx->cl_status, 8));
-    int32_t *bad = ptr<int32_t>(ctx->cl_status);
-    fill_i64(ptr<int64_t>(ctx->cl_status), 0, 1, s);
-    launch_check_csr(a.offsets, n, bad, s);
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, a.offsets + n, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar + 1, bad, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    const int64_t n_cand = ctx->host_scalar[0];
-    int32_t b0 = 0;
-    memcpy(&b0, ctx->host_scalar + 1, 4);
-    if (b0) return fail(ctx, PETAR_E_INVALID, "candidate offsets must start at 0 and not decrease");
-    if (out_idx == nullptr) {  // internal output sized to the candidates
-        TRY(ensure(ctx, ctx->grp_idx, (size_t)(n_cand > 0 ? n_cand : 1) * 4));
-        out_idx = ptr<int32_t>(ctx->grp_idx);
-        capacity = n_cand;
-    }
-    TRY(ensure(ctx, ctx->cl_keep, (size_t)(n_cand > 0 ? n_cand : 1)));
-    TRY(ensure(ctx, ctx->cl_row, (size_t)(n_cand > 0 ? n_cand : 1) * 4));
     TRY(ensure(ctx, ctx->cl_counts, (size_t)(n + 1) * 4));
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_ws_elems(n + 1) * 8));
-    launch_filter(a, n_cand, ptr<int32_t>(ctx->cl_row), ptr<uint8_t>(ctx->cl_keep),
-                  ptr<uint32_t>(ctx->cl_counts), bad, s);
-    scan_u32_to_i64(ptr<uint32_t>(ctx->cl_counts), out_offsets, n, ptr<int64_t>(ctx->scan_ws), s);
-    launch_filter_write(a, ptr<uint8_t>(ctx->cl_keep), out_offsets, out_idx, capacity, s);
-    HIP_TRY(ctx, hipGetLastError());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, out_offsets + n, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar + 1, bad, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    int32_t b = 0;
-    memcpy(&b, ctx->host_scalar + 1, 4);
-    if (b) return fail(ctx, PETAR_E_INVALID, "candidate index outside [0, N)");
-    *required = ctx->host_scalar[0];
-    if (*required > capacity)
-        return fail(ctx, PETAR_E_NB_OVERFLOW, "neighbour capacity %lld < required %lld",
-                    (long long)capacity, (long long)*required);
-    return PETAR_OK;
+    // records when there is room for them (they only save time)
+    double *rec = nullptr;
+    const size_t rec_bytes = (size_t)n * (size_t)filter_rec_doubles(a.mode) * 8;
+    if (room_for(ctx, ctx->cl_rec, rec_bytes)) {
+        TRY(ensure(ctx, ctx->cl_rec, rec_bytes));
+        rec = ptr<double>(ctx->cl_rec);
+    }
+    // first guesses: 16 candidates a star, 4 of them kept
+    const size_t guess = (size_t)filter_words(n, 16 * n) * 8, guess_idx = (size_t)n * 16;
+    if (ctx->cl_masks.cap < guess && room_for(ctx, ctx->cl_masks, guess))
+        TRY(ensure(ctx, ctx->cl_masks, guess));
+    if (own && ctx->grp_idx.cap < guess_idx && room_for(ctx, ctx->grp_idx, guess_idx))
+        TRY(ensure(ctx, ctx->grp_idx, guess_idx));
+    int32_t *bad = ptr<int32_t>(ctx->cl_status), *csr_bad = bad + 1;
+    while (true) {
+        if (own) {
+            out_idx = ptr<int32_t>(ctx->grp_idx);
+            capacity = (int64_t)(ctx->grp_idx.cap / 4);
+        }
+        const int64_t mask_cap = (int64_t)(ctx->cl_masks.cap / 8);
+        fill_i64(ptr<int64_t>(ctx->cl_status), 0, 1, s);
+        launch_check_csr(a.offsets, n, csr_bad, s);
+        launch_filter(a, rec, ptr<uint64_t>(ctx->cl_masks), mask_cap,
+                      ptr<uint32_t>(ctx->cl_counts), bad, csr_bad, s);
+        scan_u32_to_i64(ptr<uint32_t>(ctx->cl_counts), out_offsets, n,
+                        ptr<int64_t>(ctx->scan_ws), s);
+        launch_filter_write(a, ptr<uint64_t>(ctx->cl_masks), mask_cap, out_offsets, out_idx,
+                            capacity, bad, csr_bad, ctx->scalar_dev, s);
+        HIP_TRY(ctx, hipGetLastError());
+        HIP_TRY(ctx, hipStreamSynchronize(s));
+        const int64_t kept = ctx->host_scalar[0], n_cand = ctx->host_scalar[1],
+                      flags = ctx->host_scalar[2];
+        if (flags & 2)
+            return fail(ctx, PETAR_E_INVALID,
+                        "candidate offsets must start at 0 and not decrease");
+        if (filter_words(n, n_cand) > mask_cap) {
+            TRY(ensure(ctx, ctx->cl_masks, (size_t)filter_words(n, n_cand) * 8));
+            if (own) TRY(ensure(ctx, ctx->grp_idx, (size_t)(n_cand > 0 ? n_cand : 1) * 4));
+            continue;
+        }
+        if (flags & 1) return fail(ctx, PETAR_E_INVALID, "candidate index outside [0, N)");
+        if (own && kept > capacity) {
+            TRY(ensure(ctx, ctx->grp_idx, (size_t)n_cand * 4));
+            continue;
+        }
+        *required = kept;
+        if (kept > capacity)
+            return fail(ctx, PETAR_E_NB_OVERFLOW, "neighbour capacity %lld < required %lld",
+                        (long long)capacity, (long long)kept);
+        return PETAR_OK;
+    }
 }
 
 // Scratch of the clusters pass for n particles.
@@ -417,7 +446,7 @@ struct ClusterWs {
     uint32_t *root, *rootpos;    // [n + 1] root flags, their exclusive scan
     int32_t *flags;              // [2] bad offsets, bad index
     uint64_t *key0, *key1;       // [n] sort keys (double-buffered)
-    uint32_t *val0, *val1;       // [n] sort values
+    uint32_t *val0;              // [n] sort values (the others go to the caller's members)
     void *sort_ws;               // sort_ws_bytes(n)
     int64_t *scan_ws;            // scan_ws_elems(n + 1)
 };
@@ -440,7 +469,6 @@ size_t cluster_ws_carve(char *base, int64_t n, ClusterWs *w) {
     c.key0 = (uint64_t *)take(un * 8);
     c.key1 = (uint64_t *)take(un * 8);
     c.val0 = (uint32_t *)take(un * 4);
-    c.val1 = (uint32_t *)take(un * 4);
     c.sort_ws = take((size_t)sort_ws_bytes(n));
     c.scan_ws = (int64_t *)take((size_t)scan_ws_elems(n + 1) * 8);
     if (w) *w = c;
@@ -460,25 +488,21 @@ petar_status clusters_core(petar_ctx *ctx, int64_t n, const int64_t *nb_offsets,
     launch_components(nb_offsets, nb_idx, n, w.parent, label, w.root, bad, csr_bad, s);
     scan_u32_to_u32(w.root, w.rootpos, n, w.scan_ws, s);
     // members: stable radix sort of the particle indices by cluster index
-    uint64_t *k = w.key0, *ka = w.key1;
-    uint32_t *v = w.val0, *va = w.val1;
-    launch_cluster_keys(label, n, w.rootpos, k, v, s);
+    // (the passes alternate between two buffers and end in `members`)
     int passes = 1;
     while (passes < 4 && (n - 1) >> (8 * passes)) passes++;
+    uint64_t *k = w.key0, *ka = w.key1;
+    uint32_t *v = w.val0, *va = (uint32_t *)members;
+    if (passes % 2 == 0) std::swap(v, va);
+    launch_cluster_keys(label, n, w.rootpos, k, v, s);
     radix_sort(&k, &v, &ka, &va, n, passes, w.sort_ws, s);
-    HIP_TRY(ctx, hipMemcpyAsync(members, v, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
-    launch_cluster_offsets(k, n, cl_offsets, s);
+    launch_cluster_offsets(k, n, cl_offsets, w.rootpos + n, w.flags, ctx->scalar_dev, s);
     HIP_TRY(ctx, hipGetLastError());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, w.rootpos + n, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar + 1, csr_bad, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    int32_t fl[2] = {0, 0};
-    memcpy(fl, ctx->host_scalar + 1, 8);
-    if (fl[0]) return fail(ctx, PETAR_E_INVALID, "neighbour offsets must start at 0 and not decrease");
-    if (fl[1]) return fail(ctx, PETAR_E_INVALID, "neighbour index outside [0, N)");
-    uint32_t nc = 0;
-    memcpy(&nc, ctx->host_scalar, 4);
-    *n_clusters = nc;
+    const int64_t fl = ctx->host_scalar[1];
+    if (fl & 1) return fail(ctx, PETAR_E_INVALID, "neighbour offsets must start at 0 and not decrease");
+    if (fl & 2) return fail(ctx, PETAR_E_INVALID, "neighbour index outside [0, N)");
+    *n_clusters = ctx->host_scalar[0];
     return PETAR_OK;
 }
 
@@ -493,7 +517,6 @@ petar_status clusters_impl(petar_ctx *ctx, int64_t n, const int64_t *nb_offsets,
     TRY(ensure(ctx, ctx->cl_key0, (size_t)n * 8));
     TRY(ensure(ctx, ctx->cl_key1, (size_t)n * 8));
     TRY(ensure(ctx, ctx->cl_val0, (size_t)n * 4));
-    TRY(ensure(ctx, ctx->cl_val1, (size_t)n * 4));
     TRY(ensure(ctx, ctx->sort_ws, (size_t)sort_ws_bytes(n)));
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_ws_elems(n + 1) * 8));
     ClusterWs w;
@@ -504,7 +527,6 @@ petar_status clusters_impl(petar_ctx *ctx, int64_t n, const int64_t *nb_offsets,
     w.key0 = ptr<uint64_t>(ctx->cl_key0);
     w.key1 = ptr<uint64_t>(ctx->cl_key1);
     w.val0 = ptr<uint32_t>(ctx->cl_val0);
-    w.val1 = ptr<uint32_t>(ctx->cl_val1);
     w.sort_ws = ctx->sort_ws.p;
     w.scan_ws = ptr<int64_t>(ctx->scan_ws);
     return clusters_core(ctx, n, nb_offsets, nb_idx, label, cl_offsets, members, n_clusters, w);
@@ -590,13 +612,11 @@ petar_status petar_groups(petar_ctx *ctx, int64_t n, const double *pos, const do
     uint32_t *flag = ptr<uint32_t>(ctx->art_single), *where = ptr<uint32_t>(ctx->art_spos);
     launch_group_pairs(grp_offsets, members, ng, pos, vel, mass, n, ctx->params.G, flag, s);
     scan_u32_to_u32(flag, where, ng, ptr<int64_t>(ctx->scan_ws), s);
-    launch_group_pairs_write(grp_offsets, members, ng, flag, where, pairs, pair_cap, s);
+    launch_group_pairs_write(grp_offsets, members, ng, flag, where, pairs, pair_cap,
+                             ctx->scalar_dev, s);
     HIP_TRY(ctx, hipGetLastError());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, where + ng, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    uint32_t np = 0;
-    memcpy(&np, ctx->host_scalar, 4);
-    *n_pairs = np;
+    *n_pairs = ctx->host_scalar[0];
     return PETAR_OK;
 }
 

@@ -10,8 +10,8 @@
 // ones. FP64 without contraction, in this exact order, so that every
 // decision is reproducible by any implementation of the same formula.
 //
-// Clusters: connected components of the kept pairs by a one-pass union-find
-// whose roots are the smallest index of each component (so the result does
+// Clusters: connected components of the kept pairs by a union-find whose
+// roots are the smallest index of each component (so the result does
 // not depend on the order of the unions).
 #include <mutex>
 
@@ -86,77 +86,179 @@ __global__ __launch_bounds__(kThreads) void k_check_csr(const int64_t *offsets, 
     if (__ballot(b) && lane_id() == 0) atomicOr(bad, 1);
 }
 
-// Row of every candidate entry (one thread per row; rows are short).
-__global__ __launch_bounds__(kThreads) void k_filter_rows(FilterArgs a, int32_t *row) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        for (int64_t e = a.offsets[i]; e < a.offsets[i + 1]; e++) row[e] = (int32_t)i;
-}
+// The rows of a CSR by waves: a wave takes 64 consecutive rows, whose
+// entries are consecutive, 64 entries at a time, one per lane. Rows differ
+// widely (a massive star has a thousand neighbours, most have a few), and a
+// thread per row took as long as the longest row: at 100k stars the passes
+// of this file ran 20 to 260 us each, now 5 to 20.
+struct RowLds {
+    uint32_t head[kWave];  // row + 1 that starts at an entry of the chunk
+};
 
-// keep[e] for every candidate entry (one thread per entry, so the gathers
-// of the partners' data overlap); an index outside [0, n) raises *bad.
-__global__ __launch_bounds__(kThreads) void k_filter_test(FilterArgs a, const int32_t *row,
-                                                          int64_t n_cand, uint8_t *keep,
-                                                          int32_t *bad) {
-    const int64_t n = a.n;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_cand;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = row[e], j = a.idx[e];
-        if (j < 0 || j >= n) {
-            atomicOr(bad, 1);
-            keep[e] = 0;
-            continue;
-        }
-        if (a.mode == 1) {
-            keep[e] = group_pair(a.pos[i], a.pos[n + i], a.pos[2 * n + i], a.r_nb[i], a.pos[j],
-                                 a.pos[n + j], a.pos[2 * n + j], a.r_nb[j], a.c_v)
-                          ? 1
-                          : 0;
-            continue;
-        }
-        const double rp = pericentre(a.pos[i], a.pos[n + i], a.pos[2 * n + i], a.vel[i],
-                                     a.vel[n + i], a.vel[2 * n + i], a.mass[i], a.pos[j],
-                                     a.pos[n + j], a.pos[2 * n + j], a.vel[j], a.vel[n + j],
-                                     a.vel[2 * n + j], a.mass[j], a.G);
-        keep[e] = rp < a.c_v * a.r_nb[i] ? 1 : 0;
+struct RowWave {
+    int64_t r0, e0, e1;  // first row, entry range
+    int64_t beg, end;    // this lane's row
+    uint32_t carry;      // last row + 1 seen so far
+    RowLds *L;
+
+    __device__ __forceinline__ void open(const int64_t *offsets, int64_t n, int64_t block,
+                                         RowLds *l) {
+        L = l;
+        r0 = block * kWave;
+        const int64_t r = r0 + lane_id();
+        beg = offsets[r < n ? r : n];
+        end = offsets[r + 1 < n ? r + 1 : n];
+        const int64_t last = r0 + kWave < n ? r0 + kWave : n;
+        e0 = offsets[r0];
+        e1 = offsets[last];
+        carry = 0;
     }
-}
-
-__global__ __launch_bounds__(kThreads) void k_filter_count(FilterArgs a, const uint8_t *keep,
-                                                           uint32_t *counts) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t c = 0;
-        for (int64_t e = a.offsets[i]; e < a.offsets[i + 1]; e++) c += keep[e];
-        counts[i] = c;
+    // Row (0..63) of the entry base + lane; base goes from e0 to e1 by 64.
+    // Lanes past the last entry get the last row.
+    __device__ __forceinline__ int row(int64_t base) {
+        wave_sync();
+        L->head[lane_id()] = 0u;
+        wave_sync();
+        if (end > beg && beg >= base && beg < base + kWave)
+            L->head[beg - base] = (uint32_t)lane_id() + 1u;
+        wave_sync();
+        uint32_t v = wave_incl_max(L->head[lane_id()]);
+        v = v > carry ? v : carry;
+        carry = last_lane(v);
+        return (int)v - 1;
     }
+};
+
+inline unsigned row_grid(int64_t n) {
+    return grid_for((n + kWave - 1) / kWave, kThreads / kWave, 16384);
 }
 
-__global__ __launch_bounds__(kThreads) void k_filter_write(FilterArgs a, const uint8_t *keep,
-                                                           const int64_t *out_offsets,
-                                                           int32_t *out_idx, int64_t capacity) {
+// What the test reads of a star, in one record (64 B, or 32 B for the group
+// relation) instead of seven (four) arrays: a candidate's partner is
+// anywhere, and every array costs a memory transaction of its own.
+__global__ __launch_bounds__(kThreads) void k_filter_pack(FilterArgs a, double4 *rec) {
     const int64_t n = a.n;
-    if (out_offsets[n] > capacity) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t w = out_offsets[i];
-        for (int64_t e = a.offsets[i]; e < a.offsets[i + 1]; e++)
-            if (keep[e]) out_idx[w++] = a.idx[e];
+        const double4 p = make_double4(a.pos[i], a.pos[n + i], a.pos[2 * n + i], a.r_nb[i]);
+        if (a.mode == 1) {
+            rec[i] = p;
+        } else {
+            rec[2 * i] = p;
+            rec[2 * i + 1] = make_double4(a.vel[i], a.vel[n + i], a.vel[2 * n + i], a.mass[i]);
+        }
+    }
+}
+
+// Decision of every candidate entry: its bit in masks (one word per chunk of
+// 64 entries, the chunks of row block b starting at word b + offsets[64 b] /
+// 64) and the kept entries per row. An index outside [0, n) raises *bad.
+// Nothing is done when the CSR check failed or the words do not fit. kRec:
+// from the records of k_filter_pack, else from the arrays.
+template <int MODE, bool kRec>
+__global__ __launch_bounds__(kThreads) void k_filter_test(FilterArgs a, const double4 *rec,
+                                                          uint64_t *masks, int64_t mask_cap,
+                                                          uint32_t *counts, int32_t *bad,
+                                                          const int32_t *csr_bad) {
+    __shared__ RowLds lds[kThreads / kWave];
+    __shared__ uint32_t kept[kThreads / kWave][kWave];
+    const int64_t n = a.n;
+    if (*csr_bad || filter_words(n, a.offsets[n]) > mask_cap) return;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t nblk = (n + kWave - 1) / kWave;
+    auto point = [&](int64_t i) {
+        if constexpr (kRec) return rec[MODE == 1 ? i : 2 * i];
+        return make_double4(a.pos[i], a.pos[n + i], a.pos[2 * n + i], a.r_nb[i]);
+    };
+    auto motion = [&](int64_t i) {
+        if constexpr (kRec) return rec[2 * i + 1];
+        return make_double4(a.vel[i], a.vel[n + i], a.vel[2 * n + i], a.mass[i]);
+    };
+    for (int64_t blk = (int64_t)blockIdx.x * (kThreads / kWave) + w; blk < nblk;
+         blk += (int64_t)gridDim.x * (kThreads / kWave)) {
+        RowWave rows;
+        rows.open(a.offsets, n, blk, &lds[w]);
+        wave_sync();
+        kept[w][lane] = 0u;
+        int64_t word = blk + rows.e0 / kWave;
+        for (int64_t base = rows.e0; base < rows.e1; base += kWave, word++) {
+            const int row = rows.row(base);
+            const int64_t e = base + lane;
+            bool keep = false;
+            if (e < rows.e1) {
+                const int64_t i = rows.r0 + row, j = a.idx[e];
+                if (j < 0 || j >= n) {
+                    atomicOr(bad, 1);
+                } else {
+                    const double4 pi = point(i), pj = point(j);
+                    if constexpr (MODE == 1) {
+                        keep = group_pair(pi.x, pi.y, pi.z, pi.w, pj.x, pj.y, pj.z, pj.w, a.c_v);
+                    } else {
+                        const double4 vi = motion(i), vj = motion(j);
+                        keep = pericentre(pi.x, pi.y, pi.z, vi.x, vi.y, vi.z, vi.w, pj.x, pj.y,
+                                          pj.z, vj.x, vj.y, vj.z, vj.w, a.G) < a.c_v * pi.w;
+                    }
+                }
+                if (keep) atomicAdd(&kept[w][row], 1u);
+            }
+            const uint64_t m = __ballot(keep);
+            if (lane == 0) masks[word] = m;
+        }
+        wave_sync();
+        if (rows.r0 + lane < n) counts[rows.r0 + lane] = kept[w][lane];
+    }
+}
+
+// The kept entries of a row block are consecutive in the output too. Also
+// the words the host reads: host[0] = kept entries, host[1] = candidates,
+// host[2] = bad index, bad CSR.
+__global__ __launch_bounds__(kThreads) void k_filter_write(FilterArgs a, const uint64_t *masks,
+                                                           int64_t mask_cap,
+                                                           const int64_t *out_offsets,
+                                                           int32_t *out_idx, int64_t capacity,
+                                                           const int32_t *bad,
+                                                           const int32_t *csr_bad, int64_t *host) {
+    const int64_t n = a.n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        host[0] = out_offsets[n];
+        host[1] = *csr_bad ? 0 : a.offsets[n];
+        host[2] = (*bad ? 1 : 0) | (*csr_bad ? 2 : 0);
+    }
+    if (*csr_bad || filter_words(n, a.offsets[n]) > mask_cap || out_offsets[n] > capacity) return;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t nblk = (n + kWave - 1) / kWave;
+    for (int64_t blk = (int64_t)blockIdx.x * (kThreads / kWave) + w; blk < nblk;
+         blk += (int64_t)gridDim.x * (kThreads / kWave)) {
+        const int64_t r0 = blk * kWave, last = r0 + kWave < n ? r0 + kWave : n;
+        const int64_t e0 = a.offsets[r0], e1 = a.offsets[last];
+        int64_t o = out_offsets[r0], word = blk + e0 / kWave;
+        for (int64_t base = e0; base < e1; base += kWave, word++) {
+            const unsigned long long m = masks[word];
+            if (m >> lane & 1ull) out_idx[o + lanes_below(m)] = a.idx[base + lane];
+            o += __popcll(m);
+        }
     }
 }
 
 // ------------------------------------------------------------ components
-// Union-find over the pairs in one pass. Every parent pointer goes to a
-// smaller index (parent[v] <= v), so a root is the smallest index of its
-// tree. rep() follows the pointers and halves the path behind it with plain
+// Union-find over the pairs. Every parent pointer goes to a smaller index
+// (parent[v] <= v), so a root is the smallest index of its tree, and a union
+// links the larger of two roots under the smaller with a compare-and-swap;
+// after all unions each component is one tree whose root is its smallest
+// index, whatever the order.
+// The pairs are taken in four passes: each star's smallest neighbour (no
+// swap needed), its first, its last, and then all, with the trees flattened
+// in between. A pass reads the roots that the flattening left (a load inside
+// a launch may return an older parent, since the L2 caches of the XCDs are
+// not coherent within it) and goes on from there with loads and swaps at the
+// coherence point. In one pass, every pair inside a percolating cluster
+// climbed from its stars' old roots to the common root with swaps on the
+// same few words, 2.7 ms at a million stars; after the sampling passes
+// nearly all stars of such a cluster have the same root, and their pairs
+// end with one comparison (0.1 ms).
+// rep() follows the pointers and halves the path behind it with plain
 // stores, which only ever replace a non-root's parent by one of its
-// ancestors; a union links the larger of two roots under the smaller with a
-// compare-and-swap, and a failed swap continues from the value it returns
-// (a smaller ancestor), so the loop ends. Plain loads may return older,
-// larger ancestors (caches of other XCDs are not coherent inside a
-// launch): the chain still leads into the same tree, and every link is
-// checked by the swap at the coherence point. After all unions each
-// component is one tree whose root is its smallest index.
+// ancestors (used where no swap runs at the same time).
 __device__ __forceinline__ int32_t uf_rep(int32_t *parent, int32_t v) {
     int32_t cur = parent[v];
     if (cur == v) return v;
@@ -174,20 +276,31 @@ __device__ __forceinline__ int32_t uf_rep(int32_t *parent, int32_t v) {
 __global__ __launch_bounds__(kThreads) void k_uf_init(const int64_t *offsets, const int32_t *idx,
                                                       int64_t n, int32_t *parent,
                                                       const int32_t *csr_bad) {
+    __shared__ RowLds lds[kThreads / kWave];
+    __shared__ int32_t low[kThreads / kWave][kWave];
     if (*csr_bad) return;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        int32_t m = (int32_t)v;
-        for (int64_t e = offsets[v]; e < offsets[v + 1]; e++) {
-            const int32_t u = idx[e];
-            if (u >= 0 && u < m) m = u;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t nblk = (n + kWave - 1) / kWave;
+    for (int64_t blk = (int64_t)blockIdx.x * (kThreads / kWave) + w; blk < nblk;
+         blk += (int64_t)gridDim.x * (kThreads / kWave)) {
+        RowWave rows;
+        rows.open(offsets, n, blk, &lds[w]);
+        wave_sync();
+        low[w][lane] = (int32_t)(rows.r0 + lane);
+        for (int64_t base = rows.e0; base < rows.e1; base += kWave) {
+            const int row = rows.row(base);
+            if (base + lane < rows.e1) {
+                const int32_t u = idx[base + lane];
+                if (u >= 0 && u < rows.r0 + row) atomicMin(&low[w][row], u);
+            }
         }
-        parent[v] = m;
+        wave_sync();
+        if (rows.r0 + lane < n) parent[rows.r0 + lane] = low[w][lane];
     }
 }
 
-// Every particle straight to the end of its chain after the init, so that
-// the finds of the union pass start from flat trees.
+// Every particle straight to the end of its chain, so that the next pass
+// starts from flat trees.
 __global__ __launch_bounds__(kThreads) void k_uf_flatten(int32_t *parent, int64_t n,
                                                          const int32_t *csr_bad) {
     if (*csr_bad) return;
@@ -196,29 +309,56 @@ __global__ __launch_bounds__(kThreads) void k_uf_flatten(int32_t *parent, int64_
         parent[v] = uf_rep(parent, (int32_t)v);
 }
 
-__global__ __launch_bounds__(kThreads) void k_uf_union(const int64_t *offsets, const int32_t *idx,
-                                                       int64_t n, int32_t *parent, int32_t *bad,
-                                                       const int32_t *csr_bad) {
+// Joins the trees of a and b, ancestors of two stars (or the stars).
+__device__ __forceinline__ void uf_join(int32_t *parent, int32_t a, int32_t b) {
+    while (a != b) {
+        if (a < b) {
+            const int32_t t = a;
+            a = b;
+            b = t;
+        }
+        int32_t p = __hip_atomic_load(parent + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (p == a) {
+            p = atomicCAS(parent + a, a, b);
+            if (p == a) return;
+        }
+        a = p;  // a smaller ancestor of a
+    }
+}
+
+// One pair per row: its first entry, or its last.
+__global__ __launch_bounds__(kThreads) void k_uf_sample(const int64_t *offsets, const int32_t *idx,
+                                                        int64_t n, int32_t *parent, bool last,
+                                                        const int32_t *csr_bad) {
     if (*csr_bad) return;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x) {
-        for (int64_t e = offsets[v]; e < offsets[v + 1]; e++) {
-            const int32_t u = idx[e];
-            if (u < 0 || u >= n) {
-                atomicOr(bad, 1);
-                continue;
-            }
-            int32_t vr = uf_rep(parent, (int32_t)v), ur = uf_rep(parent, u);
-            while (vr != ur) {
-                if (vr < ur) {
-                    const int32_t old = atomicCAS(parent + ur, ur, vr);
-                    if (old == ur) break;
-                    ur = old;
-                } else {
-                    const int32_t old = atomicCAS(parent + vr, vr, ur);
-                    if (old == vr) break;
-                    vr = old;
-                }
+        const int64_t beg = offsets[v], end = offsets[v + 1];
+        if (beg == end) continue;
+        const int32_t u = idx[last ? end - 1 : beg];
+        if (u >= 0 && u < n) uf_join(parent, parent[v], parent[u]);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_uf_union(const int64_t *offsets, const int32_t *idx,
+                                                       int64_t n, int32_t *parent, int32_t *bad,
+                                                       const int32_t *csr_bad) {
+    __shared__ RowLds lds[kThreads / kWave];
+    if (*csr_bad) return;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t nblk = (n + kWave - 1) / kWave;
+    for (int64_t blk = (int64_t)blockIdx.x * (kThreads / kWave) + w; blk < nblk;
+         blk += (int64_t)gridDim.x * (kThreads / kWave)) {
+        RowWave rows;
+        rows.open(offsets, n, blk, &lds[w]);
+        for (int64_t base = rows.e0; base < rows.e1; base += kWave) {
+            const int64_t v = rows.r0 + rows.row(base);
+            if (base + lane < rows.e1) {
+                const int32_t u = idx[base + lane];
+                if (u < 0 || u >= n)
+                    atomicOr(bad, 1);
+                else
+                    uf_join(parent, parent[v], parent[u]);
             }
         }
     }
@@ -250,12 +390,22 @@ __global__ __launch_bounds__(kThreads) void k_cl_keys(const int32_t *label, int6
 }
 
 // Cluster offsets from the sorted cluster indices: a cluster starts where
-// its index first appears (entries past the last cluster stay n).
+// its index first appears; entries past the last cluster are n. Also the
+// words the host reads: host[0] = clusters, host[1] = the two flags.
 __global__ __launch_bounds__(kThreads) void k_cl_offsets(const uint64_t *key, int64_t n,
-                                                         int64_t *cl_offsets) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        if (i == 0 || key[i] != key[i - 1]) cl_offsets[key[i]] = i;
+                                                         int64_t *cl_offsets,
+                                                         const uint32_t *n_clusters,
+                                                         const int32_t *flags, int64_t *host) {
+    const int64_t nc = *n_clusters;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (i >= nc) cl_offsets[i] = n;
+        if (i < n && (i == 0 || key[i] != key[i - 1])) cl_offsets[key[i]] = i;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        host[0] = nc;
+        host[1] = (flags[0] ? 1 : 0) | (flags[1] ? 2 : 0);
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void k_group_pairs(const int64_t *off, const int32_t *mem,
@@ -285,7 +435,9 @@ __global__ __launch_bounds__(kThreads) void k_group_pairs_write(const int64_t *o
                                                                 int64_t n_groups,
                                                                 const uint32_t *is_pair,
                                                                 const uint32_t *pos,
-                                                                int32_t *pairs, int64_t cap) {
+                                                                int32_t *pairs, int64_t cap,
+                                                                int64_t *host) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) host[0] = pos[n_groups];
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_groups;
          g += (int64_t)gridDim.x * blockDim.x) {
         if (!is_pair[g]) continue;
@@ -306,10 +458,10 @@ void launch_group_pairs(const int64_t *grp_offsets, const int32_t *members, int6
 
 void launch_group_pairs_write(const int64_t *grp_offsets, const int32_t *members, int64_t n_groups,
                               const uint32_t *is_pair, const uint32_t *pos, int32_t *pairs,
-                              int64_t pair_cap, hipStream_t s) {
+                              int64_t pair_cap, int64_t *host, hipStream_t s) {
     hipLaunchKernelGGL(k_group_pairs_write, dim3(grid_for(n_groups, kThreads, 8192)),
                        dim3(kThreads), 0, s, grp_offsets, members, n_groups, is_pair, pos, pairs,
-                       pair_cap);
+                       pair_cap, host);
 }
 
 void launch_check_csr(const int64_t *offsets, int64_t n, int32_t *bad, hipStream_t s) {
@@ -317,28 +469,49 @@ void launch_check_csr(const int64_t *offsets, int64_t n, int32_t *bad, hipStream
                        offsets, n, bad);
 }
 
-void launch_filter(const FilterArgs &a, int64_t n_cand, int32_t *row, uint8_t *keep,
-                   uint32_t *counts, int32_t *bad, hipStream_t s) {
-    const dim3 g(grid_for(a.n, kThreads, 8192)), b(kThreads);
-    hipLaunchKernelGGL(k_filter_rows, g, b, 0, s, a, row);
-    hipLaunchKernelGGL(k_filter_test, dim3(grid_for(n_cand, kThreads, 16384)), b, 0, s, a,
-                       (const int32_t *)row, n_cand, keep, bad);
-    hipLaunchKernelGGL(k_filter_count, g, b, 0, s, a, (const uint8_t *)keep, counts);
+void launch_filter(const FilterArgs &a, double *rec, uint64_t *masks, int64_t mask_cap,
+                   uint32_t *counts, int32_t *bad, const int32_t *csr_bad, hipStream_t s) {
+    const dim3 g(row_grid(a.n)), b(kThreads);
+    double4 *r = reinterpret_cast<double4 *>(rec);
+    if (rec)
+        hipLaunchKernelGGL(k_filter_pack, dim3(grid_for(a.n, kThreads, 8192)), b, 0, s, a, r);
+#define TEST(MODE, REC)                                                                        \
+    hipLaunchKernelGGL((k_filter_test<MODE, REC>), g, b, 0, s, a, (const double4 *)r, masks,   \
+                       mask_cap, counts, bad, csr_bad)
+    if (a.mode == 1) {
+        if (rec)
+            TEST(1, true);
+        else
+            TEST(1, false);
+    } else {
+        if (rec)
+            TEST(0, true);
+        else
+            TEST(0, false);
+    }
+#undef TEST
 }
 
-void launch_filter_write(const FilterArgs &a, const uint8_t *keep, const int64_t *out_offsets,
-                         int32_t *out_idx, int64_t capacity, hipStream_t s) {
-    hipLaunchKernelGGL(k_filter_write, dim3(grid_for(a.n, kThreads, 8192)), dim3(kThreads), 0, s,
-                       a, keep, out_offsets, out_idx, capacity);
+void launch_filter_write(const FilterArgs &a, const uint64_t *masks, int64_t mask_cap,
+                         const int64_t *out_offsets, int32_t *out_idx, int64_t capacity,
+                         const int32_t *bad, const int32_t *csr_bad, int64_t *host,
+                         hipStream_t s) {
+    hipLaunchKernelGGL(k_filter_write, dim3(row_grid(a.n)), dim3(kThreads), 0, s, a, masks,
+                       mask_cap, out_offsets, out_idx, capacity, bad, csr_bad, host);
 }
 
 void launch_components(const int64_t *offsets, const int32_t *idx, int64_t n, int32_t *parent,
                        int32_t *label, uint32_t *is_root, int32_t *bad, const int32_t *csr_bad,
                        hipStream_t s) {
     const dim3 g(grid_for(n, kThreads, 8192)), b(kThreads);
-    hipLaunchKernelGGL(k_uf_init, g, b, 0, s, offsets, idx, n, parent, csr_bad);
+    const dim3 gr(row_grid(n));
+    hipLaunchKernelGGL(k_uf_init, gr, b, 0, s, offsets, idx, n, parent, csr_bad);
+    for (int last = 0; last < 2; last++) {
+        hipLaunchKernelGGL(k_uf_flatten, g, b, 0, s, parent, n, csr_bad);
+        hipLaunchKernelGGL(k_uf_sample, g, b, 0, s, offsets, idx, n, parent, last != 0, csr_bad);
+    }
     hipLaunchKernelGGL(k_uf_flatten, g, b, 0, s, parent, n, csr_bad);
-    hipLaunchKernelGGL(k_uf_union, g, b, 0, s, offsets, idx, n, parent, bad, csr_bad);
+    hipLaunchKernelGGL(k_uf_union, gr, b, 0, s, offsets, idx, n, parent, bad, csr_bad);
     hipLaunchKernelGGL(k_uf_label, g, b, 0, s, parent, n, label, is_root, csr_bad);
 }
 
@@ -349,10 +522,10 @@ void launch_cluster_keys(const int32_t *label, int64_t n, const uint32_t *root_p
 }
 
 void launch_cluster_offsets(const uint64_t *sorted_key, int64_t n, int64_t *cl_offsets,
+                            const uint32_t *n_clusters, const int32_t *flags, int64_t *host,
                             hipStream_t s) {
-    fill_i64(cl_offsets, n, n + 1, s);
-    hipLaunchKernelGGL(k_cl_offsets, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, s,
-                       sorted_key, n, cl_offsets);
+    hipLaunchKernelGGL(k_cl_offsets, dim3(grid_for(n + 1, kThreads, 8192)), dim3(kThreads), 0, s,
+                       sorted_key, n, cl_offsets, n_clusters, flags, host);
 }
 
 namespace {

@@ -103,6 +103,19 @@ __device__ __forceinline__ uint32_t wave_incl_scan<uint32_t>(uint32_t v) {
     return (uint32_t)wave_incl_scan_dpp((int)v);
 }
 
+// Inclusive prefix maximum across the 64 lanes of a wave, on DPP lane moves
+// (see wave_incl_scan_dpp; lanes without a source take 0).
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
+    auto step = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+
 // Value of the last lane (e.g. the total of an inclusive scan), wave-uniform.
 __device__ __forceinline__ uint32_t last_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);

@@ -215,10 +215,24 @@ struct FilterArgs {
 };
 // *bad |= (offsets[0] != 0 or offsets decrease somewhere)
 void launch_check_csr(const int64_t *offsets, int64_t n, int32_t *bad, hipStream_t s);
-void launch_filter(const FilterArgs &a, int64_t n_cand, int32_t *row, uint8_t *keep,
-                   uint32_t *counts, int32_t *bad, hipStream_t s);
-void launch_filter_write(const FilterArgs &a, const uint8_t *keep, const int64_t *out_offsets,
-                         int32_t *out_idx, int64_t capacity, hipStream_t s);
+// Words that hold one bit per candidate entry (a word per 64 entries of each
+// block of 64 rows).
+__host__ __device__ inline int64_t filter_words(int64_t n, int64_t n_cand) {
+    return (n + kWave - 1) / kWave + n_cand / kWave + 1;
+}
+// Doubles per star in the records of the test (rec, or null: the arrays are
+// read instead).
+inline int64_t filter_rec_doubles(int mode) { return mode == 1 ? 4 : 8; }
+// Decisions as bits (masks, mask_cap words) and kept entries per row; then
+// the kept entries in place, with the words host (pinned) = kept entries,
+// candidates, (bad index) | (bad CSR) << 1. Neither does anything when
+// *csr_bad or when the decisions need more than mask_cap words.
+void launch_filter(const FilterArgs &a, double *rec, uint64_t *masks, int64_t mask_cap,
+                   uint32_t *counts, int32_t *bad, const int32_t *csr_bad, hipStream_t s);
+void launch_filter_write(const FilterArgs &a, const uint64_t *masks, int64_t mask_cap,
+                         const int64_t *out_offsets, int32_t *out_idx, int64_t capacity,
+                         const int32_t *bad, const int32_t *csr_bad, int64_t *host,
+                         hipStream_t s);
 // Components of a neighbour CSR (pairs taken both ways): label[i] =
 // smallest index of i's component, is_root[i] = (label[i] == i); parent is
 // scratch [n]; *bad |= an index outside [0, n). Nothing runs when *csr_bad.
@@ -230,7 +244,9 @@ void launch_components(const int64_t *offsets, const int32_t *idx, int64_t n, in
 // ascending order; cluster offsets from the sorted keys.
 void launch_cluster_keys(const int32_t *label, int64_t n, const uint32_t *root_pos, uint64_t *key,
                          uint32_t *val, hipStream_t s);
+// Also the words host (pinned) = clusters, flags[0] | flags[1] << 1.
 void launch_cluster_offsets(const uint64_t *sorted_key, int64_t n, int64_t *cl_offsets,
+                            const uint32_t *n_clusters, const int32_t *flags, int64_t *host,
                             hipStream_t s);
 // Fixed device scratch of petar_clusters_noalloc: one array of
 // kNoAllocScratchBytes per device, in the code object's static data, so the
@@ -245,10 +261,11 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
 void launch_group_pairs(const int64_t *grp_offsets, const int32_t *members, int64_t n_groups,
                         const double *pos, const double *vel, const double *mass, int64_t n,
                         double G, uint32_t *is_pair, hipStream_t s);
-// pairs[pos[g]] and pairs[pair_cap + pos[g]] for every flagged group.
+// pairs[pos[g]] and pairs[pair_cap + pos[g]] for every flagged group; *host
+// (pinned) = pos[n_groups].
 void launch_group_pairs_write(const int64_t *grp_offsets, const int32_t *members, int64_t n_groups,
                               const uint32_t *is_pair, const uint32_t *pos, int32_t *pairs,
-                              int64_t pair_cap, hipStream_t s);
+                              int64_t pair_cap, int64_t *host, hipStream_t s);
 
 // --------------------------------------------------------- artificial.hip
 // Set of the long-range force with artificial particles: singles first (input

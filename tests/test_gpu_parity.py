@@ -1492,3 +1492,42 @@ def test_force_by_teams(pt, ctx, orc, n, group, leaf):
     a_dir, _ = orc.force_long(c.pos, mass, rin, rout, idx=np.nonzero(target)[0])
     assert rel_err(sub[:, target], a_dir).max() < 1e-12
     assert not sub[:, ~target].any()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 4161])
+def test_filter_and_clusters_row_shapes(pt, orc, n):
+    """Rows of every length around the 64 entries that a wave takes at once
+    (none, 1, 63, 64, 65, hundreds), first and last rows empty or long: the
+    filtered lists, clusters and groups bit-exact against the oracle, and the
+    same when the workspace cap leaves no room for the star records."""
+    c = workloads.make_cluster(n, 70 + n, imf=True, binary_fraction=0.4 if n > 1 else 0.0)
+    rng = np.random.default_rng(n)
+    length = np.minimum(rng.choice([0, 0, 1, 2, 5, 63, 64, 65, 300], n), n - 1)
+    length[-1] = min(129, n - 1)
+    offs = np.zeros(n + 1, dtype=np.int64)
+    offs[1:] = np.cumsum(length)
+    idx = np.concatenate([np.sort(rng.choice(np.delete(np.arange(n), i), k, replace=False))
+                          for i, k in enumerate(length)]).astype(np.int32)
+    rin, rout, rnb = orc.radii(c.mass, 0.2, 0.5, 1.2)
+    fo_ref, fi_ref = orc.nb_filter(c.pos, c.vel, c.mass, rnb, 1.5, offs, idx)
+    l_ref, cl_ref, m_ref = orc.clusters(n, fo_ref, fi_ref)
+    args = (T(c.pos), T(c.vel), T(c.mass))
+    results = []
+    for cap in (0, 1):
+        ctx = pt.petar_create(0)
+        if cap:  # room for everything but the records (64 B a star)
+            pt.petar_set_params(ctx, workspace_cap=used - 64 * n)
+        f_off, f_idx = pt.petar_nb_filter(ctx, *args, T(rnb), 1.5, T(offs), T(idx))
+        used = pt.petar_get_stats(ctx)["workspace_bytes"]
+        pt.petar_set_params(ctx, workspace_cap=0)
+        assert np.array_equal(f_off.cpu().numpy(), fo_ref)
+        assert np.array_equal(f_idx.cpu().numpy(), fi_ref)
+        label, cl, members = pt.petar_clusters(ctx, f_off, f_idx)
+        assert np.array_equal(label.cpu().numpy(), l_ref)
+        assert np.array_equal(cl.cpu().numpy(), cl_ref)
+        assert np.array_equal(members.cpu().numpy(), m_ref)
+        g = pt.petar_groups(ctx, args[0], args[1], args[2], T(rin), 0.5, T(offs), T(idx))
+        results.append([x.cpu().numpy() for x in g])
+        pt.petar_destroy(ctx)
+    for a, b in zip(*results):
+        assert np.array_equal(a, b)
