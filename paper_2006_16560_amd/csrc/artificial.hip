@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void k_tidal_eval(EvalArgs e) {
         const int64_t b = e.pair_of[i];
         if (b < 0) continue;
         if (b >= e.n_pair) {
-            atomicAdd(e.bad, 1);
+            *e.bad = 1;
             continue;
         }
         double rec[R];
@@ -410,6 +410,12 @@ __global__ __launch_bounds__(kThreads) void k_tidal_eval(EvalArgs e) {
         for (int d = 0; d < 3; d++) e.acc[d * e.n_pt + i] = acc[d];
         if (e.pot) e.pot[i] = pot;
     }
+}
+
+__global__ __launch_bounds__(kThreads) void k_tidal_bad(EvalArgs e, int64_t *count) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < e.n_pt;
+         i += (int64_t)gridDim.x * blockDim.x)
+        if (e.pair_of[i] >= e.n_pair) atomicAdd((unsigned long long *)count, 1ull);
 }
 
 __global__ __launch_bounds__(kThreads) void k_kick(double *vel, const double *acc, int64_t n3,
@@ -472,6 +478,11 @@ void launch_tidal_eval(const EvalArgs &e, hipStream_t s) {
         hipLaunchKernelGGL(k_tidal_eval<2>, g, b, 0, s, e);
     else
         hipLaunchKernelGGL(k_tidal_eval<3>, g, b, 0, s, e);
+}
+
+void launch_tidal_bad(const EvalArgs &e, int64_t *count, hipStream_t s) {
+    hipLaunchKernelGGL(k_tidal_bad, dim3(grid_for(e.n_pt, kThreads, 8192)), dim3(kThreads), 0, s,
+                       e, count);
 }
 
 }  // namespace petar

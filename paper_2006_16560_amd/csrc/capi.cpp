@@ -58,7 +58,8 @@ struct petar_ctx {
     uint32_t nbhead_cap = 0, nbleaf_cap = 0;
     int64_t nbrows_cap = 0;  // entries of nbrows; grown when a call's rows needed more
 
-    Status *host_status = nullptr;  // pinned
+    Status *host_status = nullptr;  // pinned; kernels write it through status_host_dev
+    Status *status_host_dev = nullptr;
     int64_t *host_scalar = nullptr; // pinned; kernels write it through scalar_dev
     int64_t *scalar_dev = nullptr;
 
@@ -192,17 +193,15 @@ TreeDev tree_view(petar_ctx *c) {
     return t;
 }
 
-void zero_status(petar_ctx *c, hipStream_t s) {
-    fill_i64(ptr<int64_t>(c->status), 0, (int64_t)(sizeof(Status) / sizeof(int64_t)), s);
-}
-
-void zero_force_status(petar_ctx *c, hipStream_t s) {
-    fill_i64(ptr<int64_t>(c->status), 0, kStatusForceWords, s);
-}
+// Words behind the emit counts: the deepest level's slots, each followed by
+// the leaves' slot.
+uint32_t *deep_slots(petar_ctx *c) { return ptr<uint32_t>(c->emit) + c->n; }
+uint32_t *leaf_slots(petar_ctx *c) { return deep_slots(c) + 1; }
 
 petar_status read_status(petar_ctx *c, hipStream_t s) {
-    HIP_TRY(c, hipMemcpyAsync(c->host_status, c->status.p, sizeof(Status), hipMemcpyDeviceToHost,
-                              s));
+    launch_status_out(ptr<Status>(c->status), leaf_slots(c), nullptr, nullptr, 0, nullptr,
+                      c->status_host_dev, s);
+    HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(s));
     return PETAR_OK;
 }
@@ -306,6 +305,8 @@ petar_status petar_create(petar_ctx **out, int device, void *hip_stream) {
         if (e == hipSuccess) e = hipHostMalloc((void **)&c->host_status, sizeof(Status));
         if (e == hipSuccess) e = hipHostMalloc((void **)&c->host_scalar, kHostScalarWords * sizeof(int64_t));
         if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->scalar_dev, c->host_scalar, 0);
+        if (e == hipSuccess)
+            e = hipHostGetDevicePointer((void **)&c->status_host_dev, c->host_status, 0);
         for (int k = 0; k < 8 && e == hipSuccess; k++) e = hipEventCreate(&c->ev[k]);
         // set-up of this device's fixed scratch (petar_clusters_noalloc)
         void *scratch_ptr = nullptr;
@@ -661,7 +662,8 @@ petar_status petar_artificial_make(petar_ctx *ctx, int64_t n, const double *pos,
     launch_art_make(a, ptr<uint32_t>(ctx->art_single), ptr<uint32_t>(ctx->art_spos),
                     ptr<int64_t>(ctx->scan_ws), bad, s);
     HIP_TRY(ctx, hipGetLastError());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, bad, 16, hipMemcpyDeviceToHost, s));
+    words_out(ptr<int64_t>(ctx->art_status), 2, ctx->scalar_dev, s);
+    HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(s));
     int32_t b[4] = {0, 0, 0, 0};
     memcpy(b, ctx->host_scalar, 16);
@@ -710,17 +712,21 @@ petar_status petar_tidal_eval(petar_ctx *ctx, int order, int64_t n_pair, const d
     if (n_pt == 0) return PETAR_OK;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
-    TRY(ensure(ctx, ctx->art_status, 16));
-    int32_t *bad = ptr<int32_t>(ctx->art_status);
-    fill_i64(ptr<int64_t>(ctx->art_status), 0, 1, s);
-    EvalArgs e{order, n_pair, tensor, frame, n_pt, pair_of, pos, acc, pot, bad};
+    ctx->host_scalar[0] = 0;  // no launch that writes it is pending
+    EvalArgs e{order, n_pair, tensor, frame, n_pt, pair_of, pos, acc, pot, ctx->scalar_dev};
     launch_tidal_eval(e, s);
     HIP_TRY(ctx, hipGetLastError());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_scalar, bad, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    int32_t b = 0;
-    memcpy(&b, ctx->host_scalar, 4);
-    if (b) return fail(ctx, PETAR_E_INVALID, "%d points with pair_of >= n_pair", b);
+    if (ctx->host_scalar[0]) {
+        TRY(ensure(ctx, ctx->art_status, 16));
+        fill_i64(ptr<int64_t>(ctx->art_status), 0, 1, s);
+        launch_tidal_bad(e, ptr<int64_t>(ctx->art_status), s);
+        words_out(ptr<int64_t>(ctx->art_status), 1, ctx->scalar_dev, s);
+        HIP_TRY(ctx, hipGetLastError());
+        HIP_TRY(ctx, hipStreamSynchronize(s));
+        return fail(ctx, PETAR_E_INVALID, "%lld points with pair_of >= n_pair",
+                    (long long)ctx->host_scalar[0]);
+    }
     return PETAR_OK;
 }
 
@@ -756,7 +762,7 @@ petar_status alloc_build_a(petar_ctx *ctx, const BuildArgs &a) {
     TRY(ensure(ctx, ctx->val1, N * 4));
     TRY(ensure(ctx, ctx->sort_ws, (size_t)sort_ws_bytes(a.n)));
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_need * 8));
-    TRY(ensure(ctx, ctx->bbox_part, (size_t)bbox_partial_blocks(a.n) * 6 * 8));
+    TRY(ensure(ctx, ctx->bbox_part, (size_t)bbox_partial_blocks(a.n, n_boxes) * 6 * 8));
     TRY(ensure(ctx, ctx->rootbox, sizeof(RootBox) * (size_t)n_boxes));
     TRY(ensure(ctx, ctx->status, sizeof(Status)));
     TRY(ensure(ctx, ctx->emit, (N + kDeepWords) * 4));  // + the deepest-level words
@@ -791,32 +797,33 @@ petar_status alloc_build_b(petar_ctx *ctx, int64_t node_cap) {
     return PETAR_OK;
 }
 
-// Phase A. The sorted keys end in key0 (8 passes).
-void enqueue_build_a(petar_ctx *ctx, const BuildArgs &a, hipStream_t s) {
-    zero_status(ctx, s);
+// Phase A. The sorted keys end in key0 (8 passes). head: also the words the
+// host reads between the phases (host_scalar).
+void enqueue_build_a(petar_ctx *ctx, const BuildArgs &a, hipStream_t s, bool head) {
     const int n_boxes = a.n_sys > 0 ? a.n_sys : 1;
     const int levels = a.n_sys > 0 ? kBatchLevels : kMaxLevel;
     RootBox *rb = ptr<RootBox>(ctx->rootbox);
-    fill_i64(ptr<int64_t>(ctx->rootbox), 0, (int64_t)(sizeof(RootBox) / 8) * n_boxes, s);
+    uint32_t *deep = deep_slots(ctx);
+    fill_words({{ptr<uint32_t>(ctx->status), (int64_t)(sizeof(Status) / 4)},
+                {ptr<uint32_t>(ctx->rootbox), (int64_t)(sizeof(RootBox) / 4) * n_boxes},
+                {deep, kDeepWords}},
+               s);
     uint64_t *k = ptr<uint64_t>(ctx->key0), *ka = ptr<uint64_t>(ctx->key1);
     uint32_t *v = ptr<uint32_t>(ctx->val0), *va = ptr<uint32_t>(ctx->val1);
-    if (a.n_sys > 0) {
-        const int64_t *off = ptr<int64_t>(ctx->sys_off);
-        launch_bbox_systems(a.pos, a.mass, a.n, off, a.n_sys, rb, s);
+    const int64_t *off = a.n_sys > 0 ? ptr<int64_t>(ctx->sys_off) : nullptr;
+    launch_bbox(a.pos, a.mass, a.n, off, n_boxes, ptr<double>(ctx->bbox_part), rb, s);
+    if (a.n_sys > 0)
         launch_keys_systems(a.pos, a.n, off, a.n_sys, rb, k, v, s);
-    } else {
-        launch_bbox(a.pos, a.mass, a.n, ptr<double>(ctx->bbox_part), rb, s);
+    else
         launch_keys(a.pos, a.n, rb, k, v, s);
-    }
     radix_sort(&k, &v, &ka, &va, a.n, 8, ctx->sort_ws.p, s);
     launch_gather_particles(a.pos, a.mass, v, a.n, ptr<double4>(ctx->ps), ptr<uint32_t>(ctx->orig),
                             ptr<uint32_t>(ctx->rank), s);
-    uint32_t *deep_slots = ptr<uint32_t>(ctx->emit) + a.n;
-    fill_u32(deep_slots, 0, kDeepWords, s);
-    launch_octree_count(k, a.n, a.leaf_size, levels, ptr<uint32_t>(ctx->emit), deep_slots, s);
+    launch_octree_count(k, a.n, a.leaf_size, levels, ptr<uint32_t>(ctx->emit), deep, s);
     scan_u32_to_i64(ptr<uint32_t>(ctx->emit), ptr<int64_t>(ctx->base), a.n,
                     ptr<int64_t>(ctx->scan_ws), s);
-    launch_build_head(ptr<int64_t>(ctx->base), a.n, rb, deep_slots, ptr<Status>(ctx->status), s);
+    if (head)
+        launch_build_head(ptr<int64_t>(ctx->base), a.n, rb, deep, ctx->scalar_dev, s);
 }
 
 // Phase B with cell arrays of node_cap entries (the cell count is read on the
@@ -830,7 +837,6 @@ void enqueue_build_b(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int d
     t.n_nodes = node_cap;
     PreOrder pre = pre_view(ctx);
     Status *st = ptr<Status>(ctx->status);
-    fill_u32(pre.nchild, 0, node_cap, s);
     uint64_t *lk = ptr<uint64_t>(ctx->lkey0), *lka = ptr<uint64_t>(ctx->lkey1);
     uint32_t *lv = ptr<uint32_t>(ctx->lval0), *lva = ptr<uint32_t>(ctx->lval1);
     const uint64_t *k = ptr<uint64_t>(ctx->key0);
@@ -838,10 +844,9 @@ void enqueue_build_b(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int d
                         node_cap, st, s);
     radix_sort(&lk, &lv, &lka, &lva, node_cap, 1, ctx->sort_ws.p, s,
                t.n_nodes_dev);
-    launch_relayout(lv, pre, ptr<RootBox>(ctx->rootbox), k, levels, t,
-                    ptr<uint32_t>(ctx->level_off), s);
-    launch_moments(t, deep, s);
-    launch_tree_summary(t, st, s);
+    launch_relayout(lv, lk, pre, ptr<RootBox>(ctx->rootbox), k, levels, t,
+                    ptr<uint32_t>(ctx->level_off), st, leaf_slots(ctx), s);
+    launch_moments(t, deep, a.n_sys > 0 ? a.n_sys : 1, s);
 }
 
 void set_tree_state(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int deep) {
@@ -871,17 +876,17 @@ petar_status build_eager(petar_ctx *ctx, const BuildArgs &a) {
     TRY(alloc_build_a(ctx, a));
     TRY(copy_offsets(ctx, a, s));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], s));
-    enqueue_build_a(ctx, a, s);
+    enqueue_build_a(ctx, a, s, true);
     HIP_TRY(ctx, hipGetLastError());
-    TRY(read_status(ctx, s));  // cell count, input check, deepest level
-    if (ctx->host_status->bad_input)
+    HIP_TRY(ctx, hipStreamSynchronize(s));  // cell count, input check, deepest level
+    if (ctx->host_scalar[1])
         return fail(ctx, PETAR_E_INVALID, "non-finite position or mass, or negative mass");
-    const int64_t n_nodes = ctx->host_status->cells;
+    const int64_t n_nodes = ctx->host_scalar[0];
     if (n_nodes < 1 || n_nodes >= (int64_t)kNone)
         return fail(ctx, PETAR_E_INTERNAL, "cell count %lld out of range", (long long)n_nodes);
     const int levels = a.n_sys > 0 ? kBatchLevels : kMaxLevel;
-    const uint32_t deep = ctx->host_status->deep;
-    if (deep > (uint32_t)levels)
+    const int64_t deep = ctx->host_scalar[2];
+    if (deep > levels)
         return fail(ctx, PETAR_E_INTERNAL, "deepest cell level %lld out of range", (long long)deep);
     TRY(alloc_build_b(ctx, n_nodes));
     enqueue_build_b(ctx, a, n_nodes, (int)deep, s);
@@ -957,17 +962,19 @@ petar_status alloc_force(petar_ctx *ctx, const ForceArgs &a) {
 }
 
 // The neighbour passes over the near leaves handed over by the force walk
-// (the walk-based pass takes over on the device if the records overflowed).
+// (`walk`: by a walk of their own, when the hand-over overflowed), and the
+// status words to the host.
 // Rows: kBounds, the force kernel has stored each target's list bound in
 // nbcnt (input order) and their prefix sum places the rows; kRedo, the
 // rows of the previous passes again (they outgrew the scratch, which has
-// been enlarged); kExact, a counting pass first gives exact bounds (when the
-// walk's bounds ask for more rows than the scratch may hold). kRedo and
-// kExact run on the kept records and clear the pass queues and the
+// been enlarged, or the hand-over overflowed); kExact, a counting pass first
+// gives exact bounds (when the walk's bounds ask for more rows than the
+// scratch may hold). kRedo and kExact clear the pass queues and the
 // long-list count again.
 enum NbRows { kBounds, kRedo, kExact };
 
-void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbRows mode) {
+void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbRows mode,
+                bool walk) {
     const int64_t n = ctx->n;
     TreeDev t = tree_view(ctx);
     Status *st = ptr<Status>(ctx->status);
@@ -986,21 +993,26 @@ void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbR
     int64_t *ws = ptr<int64_t>(ctx->scan_ws);
     if (timed) (void)hipEventRecord(ctx->ev[6], s);
     if (mode != kBounds) fill_u32(queue + 8, 0, 8, s);
+    if (mode != kBounds) fill_u32(cnt, 0, n + 1, s);
     if (mode == kExact) {
-        fill_u32(cnt, 0, n + 1, s);
-        launch_nb_count_rec(t, rec, st, cnt, s);
-        launch_nb_write(t, groups, st, cnt, nullptr, nullptr, 0, spill, queue + 11, rec,
-                        ctx->nb_waves, s);
+        if (walk)
+            launch_nb_write(t, groups, st, cnt, nullptr, nullptr, 0, spill, queue + 11, rec,
+                            ctx->nb_waves, s);
+        else
+            launch_nb_count_rec(t, rec, st, cnt, s);
     }
-    if (mode != kRedo) scan_u32_to_i64(cnt, row_off, n, ws, s);  // bounds -> rows
-    fill_u32(cnt, 0, n + 1, s);  // the counts of the testing pass
-    launch_nb_write_rec(t, rec, st, row_off, cnt, rows, ctx->nbrows_cap, s);
-    launch_nb_write(t, groups, st, cnt, row_off, rows, ctx->nbrows_cap, spill, queue + 9, rec,
-                    ctx->nb_waves, s);
+    // bounds -> rows; cnt then takes the counts of the testing pass
+    if (mode != kRedo) scan_u32_to_i64_clear(cnt, row_off, n, ws, s);
+    if (walk)
+        launch_nb_write(t, groups, st, cnt, row_off, rows, ctx->nbrows_cap, spill, queue + 9, rec,
+                        ctx->nb_waves, s);
+    else
+        launch_nb_write_rec(t, rec, st, row_off, cnt, rows, ctx->nbrows_cap, s);
     scan_u32_to_i64(cnt, nb->offsets_dev, n, ws, s);
     launch_nb_sort(row_off, rows, nb->offsets_dev, nb->idx_dev, n, nb->capacity, st, cnt,
                    queue + 10, s);
-    launch_nb_summary(nb->offsets_dev, row_off, n, queue + kQueueRec, st, s);
+    launch_status_out(st, leaf_slots(ctx), nb->offsets_dev, row_off, n, rec.count,
+                      ctx->status_host_dev, s);
     if (timed) (void)hipEventRecord(ctx->ev[7], s);
 }
 
@@ -1015,8 +1027,7 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     Status *st = ptr<Status>(ctx->status);
     uint32_t *queue = ptr<uint32_t>(ctx->queue);
     if (timed) (void)hipEventRecord(ctx->ev[2], s);
-    zero_force_status(ctx, s);
-    fill_u32(queue, 0, kQueueWords, s);
+    fill_words({{ptr<uint32_t>(ctx->status), 2 * kStatusForceWords}, {queue, kQueueWords}}, s);
     launch_gather_radii(a.r_in, a.r_out, a.r_search, t, st, s);
     launch_rsmax(t, s);
     launch_group_flags(pre, t, a.group_size, ptr<uint32_t>(ctx->gflag), s);
@@ -1064,42 +1075,54 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     if (timed) (void)hipEventRecord(ctx->ev[4], s);
     launch_force(f, fw, s);
     if (timed) (void)hipEventRecord(ctx->ev[5], s);
-    if (a.nb) enqueue_nb(ctx, a.nb, s, timed, kBounds);
+    if (a.nb)
+        enqueue_nb(ctx, a.nb, s, timed, kBounds, false);
+    else
+        launch_status_out(st, leaf_slots(ctx), nullptr, nullptr, 0, nullptr, ctx->status_host_dev,
+                          s);
     if (timed) (void)hipEventRecord(ctx->ev[3], s);
 }
 
-// Reads the status words after a force call and fills the statistics.
+// Waits for a force call's launches, whose last one wrote the status words
+// here, and fills the statistics.
 petar_status finish_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed) {
     HIP_TRY(ctx, hipGetLastError());
-    TRY(read_status(ctx, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
     TRY(settle_build_stats(ctx, true));
     const Status &h = *ctx->host_status;
     bool exact = false;
-    if (a.nb && !h.invalid_radii && !h.stack_overflow && !h.cell_overflow &&
-        h.nb_rows > ctx->nbrows_cap) {
-        // The rows outgrew the scratch (nothing was written): enlarge it and
-        // run the neighbour passes again on the kept records (a captured
-        // graph holds the old scratch and is captured again). Rows beyond
-        // 256 entries a particle (degenerate leaves, huge search radii) or
-        // the workspace cap are not taken: exact counts bound the rows
-        // instead, which then need no more than the caller's capacity.
-        const int64_t want = h.nb_rows + h.nb_rows / 16 + 4096;
-        const int64_t limit = std::max<int64_t>(256 * ctx->n, int64_t(1) << 24);
-        const int64_t cap_bytes = ctx->params.workspace_cap;
-        const int64_t after = ctx->ws_bytes - (int64_t)ctx->nbrows.cap + want * 4;
-        exact = want > limit || (cap_bytes > 0 && after > cap_bytes);
-        if (!exact) {
-            ctx->nbrows_cap = want;
-        } else if (a.nb->capacity + 4096 > ctx->nbrows_cap) {
-            ctx->nbrows_cap = a.nb->capacity + 4096;
+    if (a.nb && !h.invalid_radii && !h.stack_overflow && !h.cell_overflow) {
+        // the hand-over overflowed: the passes run by a walk of their own
+        const bool walk = h.rec_used[0] > ctx->nbhead_cap || h.rec_used[1] > ctx->nbleaf_cap;
+        const bool outgrown = h.nb_rows > ctx->nbrows_cap;
+        if (outgrown) {
+            // The rows outgrew the scratch (nothing was written): enlarge it
+            // and run the neighbour passes again on the kept records (a
+            // captured graph holds the old scratch and is captured again).
+            // Rows beyond 256 entries a particle (degenerate leaves, huge
+            // search radii) or the workspace cap are not taken: exact counts
+            // bound the rows instead, which then need no more than the
+            // caller's capacity.
+            const int64_t want = h.nb_rows + h.nb_rows / 16 + 4096;
+            const int64_t limit = std::max<int64_t>(256 * ctx->n, int64_t(1) << 24);
+            const int64_t cap_bytes = ctx->params.workspace_cap;
+            const int64_t after = ctx->ws_bytes - (int64_t)ctx->nbrows.cap + want * 4;
+            exact = want > limit || (cap_bytes > 0 && after > cap_bytes);
+            if (!exact) {
+                ctx->nbrows_cap = want;
+            } else if (a.nb->capacity + 4096 > ctx->nbrows_cap) {
+                ctx->nbrows_cap = a.nb->capacity + 4096;
+            }
+            if ((size_t)ctx->nbrows_cap * 4 > ctx->nbrows.cap) {
+                TRY(ensure(ctx, ctx->nbrows, (size_t)ctx->nbrows_cap * 4));
+                ctx->graph_stale = true;
+            }
         }
-        if ((size_t)ctx->nbrows_cap * 4 > ctx->nbrows.cap) {
-            TRY(ensure(ctx, ctx->nbrows, (size_t)ctx->nbrows_cap * 4));
-            ctx->graph_stale = true;
+        if (outgrown || walk) {
+            enqueue_nb(ctx, a.nb, s, timed, exact ? kExact : kRedo, walk);
+            HIP_TRY(ctx, hipGetLastError());
+            HIP_TRY(ctx, hipStreamSynchronize(s));
         }
-        enqueue_nb(ctx, a.nb, s, timed, exact ? kExact : kRedo);
-        HIP_TRY(ctx, hipGetLastError());
-        TRY(read_status(ctx, s));
     }
     if (h.invalid_radii)
         return fail(ctx, PETAR_E_INVALID,
@@ -1273,7 +1296,7 @@ petar_status petar_step_graph(petar_ctx *ctx, int n_sys, const int64_t *sys_offs
         // (no stage events inside the graph: replays do not update events
         // recorded by captured nodes, so a replay is timed as a whole)
         HIP_TRY(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        enqueue_build_a(ctx, ba, cs);
+        enqueue_build_a(ctx, ba, cs, false);
         // a replay's tree may be deeper than this one: every level is launched
         const int all_levels = ba.n_sys > 0 ? kBatchLevels : kMaxLevel;
         enqueue_build_b(ctx, ba, node_cap, all_levels, cs);

@@ -41,7 +41,7 @@ struct RootBox {
     int32_t pad;
 };
 
-// Status words read back once per call. The force fields come first so a
+// Status words, written to a copy on the host once per call. The force fields come first so a
 // force call can clear them without touching the build fields.
 struct Status {
     // force
@@ -49,18 +49,15 @@ struct Status {
     int32_t stack_overflow;  // walk stack exceeded its capacity
     unsigned long long inter[3];  // pc, far, near interactions
     int64_t n_groups;
-    int64_t nb_total;        // neighbour-list entries
-    uint32_t rec_used[2];    // near-leaf hand-over claimed: headers, leaf entries
-    int64_t nb_rows;         // scratch entries the neighbour rows need
+    int64_t nb_total;        // neighbour-list entries (in the host's copy only)
+    uint32_t rec_used[2];    // near-leaf hand-over claimed: headers, leaf entries (host)
+    int64_t nb_rows;         // scratch entries the neighbour rows need (host)
     // build
     int32_t cell_overflow;   // more cells than the preallocated capacity (captured graphs)
     int32_t pad;
     int64_t n_nodes;
     int64_t n_leaves;
     int64_t max_level;
-    int64_t cells;           // cells counted by the first half of an eager build
-    int32_t bad_input;       // non-finite or negative input (the root box's count)
-    uint32_t deep;           // deepest cell level
 };
 constexpr int kStatusForceWords = 8;  // int64 words of the force fields
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "common.h"
 
 namespace petar {
@@ -13,7 +15,18 @@ namespace petar {
 // ws must hold scan_ws_elems(n) int64 values.
 int64_t scan_ws_elems(int64_t n);
 void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s);
+// The same, and the counts are 0 afterwards.
+void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s);
 void scan_u32_to_u32(const uint32_t *in, uint32_t *out, int64_t n, int64_t *ws, hipStream_t s);
+// Up to kFillPieces small buffers of 32-bit words set to 0 in one launch.
+constexpr int kFillPieces = 4;
+struct FillWords {
+    uint32_t *p;
+    int64_t words;
+};
+void fill_words(std::initializer_list<FillWords> pieces, hipStream_t s);
+// Up to 64 words to the host (pinned memory), in place of a copy.
+void words_out(const int64_t *words, int n, int64_t *host, hipStream_t s);
 void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 void fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);
 
@@ -46,14 +59,15 @@ struct PreOrder {
     uint32_t *new_of_old;
 };
 
-int bbox_partial_blocks(int64_t n);
-void launch_bbox(const double *pos, const double *mass, int64_t n, double *part, RootBox *rb,
-                 hipStream_t s);
+// Root cube of each of n_sys systems (off: their offsets on the device,
+// [n_sys + 1], or null for one system of all n); rb (zeroed) [n_sys], part
+// [bbox_partial_blocks][6].
+int bbox_partial_blocks(int64_t n, int n_sys);
+void launch_bbox(const double *pos, const double *mass, int64_t n, const int64_t *off, int n_sys,
+                 double *part, RootBox *rb, hipStream_t s);
 void launch_keys(const double *pos, int64_t n, const RootBox *rb, uint64_t *key, uint32_t *idx,
                  hipStream_t s);
 // batched mode: rb[n_sys], off = system offsets on the device [n_sys + 1]
-void launch_bbox_systems(const double *pos, const double *mass, int64_t n, const int64_t *off,
-                         int n_sys, RootBox *rb, hipStream_t s);
 void launch_keys_systems(const double *pos, int64_t n, const int64_t *off, int n_sys,
                          const RootBox *rb, uint64_t *key, uint32_t *idx, hipStream_t s);
 
@@ -75,21 +89,24 @@ constexpr int kDeepStride = 32;  // 128 B
 constexpr int kDeepWords = kDeepSlots * kDeepStride;
 void launch_octree_count(const uint64_t *key, int64_t n, int leaf_size, int levels,
                          uint32_t *emit, uint32_t *deep_slots, hipStream_t s);
-// st->cells = base[n], st->bad_input = rb->bad, st->deep = the deepest level
+// host (pinned) = cells (base[n]), bad input (rb->bad), the deepest level
 // among deep_slots (kDeepWords words).
 void launch_build_head(const int64_t *base, int64_t n, const RootBox *rb,
-                       const uint32_t *deep_slots, Status *st, hipStream_t s);
+                       const uint32_t *deep_slots, int64_t *host, hipStream_t s);
 // Pre-order cells; also the level keys (lkey, lval) sorted next.
-// Cells beyond node_cap are not written; st->cell_overflow is raised instead.
+// st->n_nodes = cells; more than node_cap are not written, but
+// st->cell_overflow is raised and st->n_nodes = 0.
 void launch_octree_write(const uint64_t *key, int64_t n, int leaf_size, int levels,
                          const int64_t *base, PreOrder pre, uint64_t *lkey, uint32_t *lval,
                          int64_t node_cap, Status *st, hipStream_t s);
 // Level-order arrays from the level-sorted permutation perm (new -> old).
-// rb holds one root box per system (one in single-system mode).
-void launch_relayout(const uint32_t *perm, PreOrder pre, const RootBox *rb, const uint64_t *key,
-                     int levels, TreeDev t, uint32_t *level_off, hipStream_t s);
-void launch_moments(const TreeDev &t, int levels, hipStream_t s);
-void launch_tree_summary(const TreeDev &t, Status *st, hipStream_t s);
+// rb holds one root box per system (one in single-system mode); lkey are the
+// sorted levels. Also the deepest level into st and the leaves, spread over
+// leaf_slots[w * kDeepStride], w < kDeepSlots (zeroed by the caller).
+void launch_relayout(const uint32_t *perm, const uint64_t *lkey, PreOrder pre, const RootBox *rb,
+                     const uint64_t *key, int levels, TreeDev t, uint32_t *level_off, Status *st,
+                     uint32_t *leaf_slots, hipStream_t s);
+void launch_moments(const TreeDev &t, int levels, int n_sys, hipStream_t s);
 
 // force_long preparation
 void launch_gather_radii(const double *r_in, const double *r_out, const double *r_search,
@@ -190,11 +207,12 @@ void launch_nb_count_rec(const TreeDev &t, const NbRecords &rec, const Status *s
 void launch_nb_write(const TreeDev &t, const uint32_t *groups, Status *st, uint32_t *cursor,
                      const int64_t *row_off, int32_t *rows, int64_t row_cap, uint32_t *spill,
                      uint32_t *queue, const NbRecords &rec, int resident_waves, hipStream_t s);
-// st->nb_total = offsets[n], st->nb_rows = row_off[n], st->rec_used =
-// rec_count[0..1] (one status copy then tells the host the list size, the
-// scratch the rows need and the hand-over use).
-void launch_nb_summary(const int64_t *offsets, const int64_t *row_off, int64_t n,
-                       const uint32_t *rec_count, Status *st, hipStream_t s);
+// The status words into host (pinned): with lists (offsets not null),
+// nb_total = offsets[n], nb_rows = row_off[n] and rec_used = rec_count[0..1];
+// n_leaves from the slots of launch_relayout.
+void launch_status_out(const Status *st, const uint32_t *leaf_slots, const int64_t *offsets,
+                       const int64_t *row_off, int64_t n, const uint32_t *rec_count, Status *host,
+                       hipStream_t s);
 void launch_nb_sort(const int64_t *row_off, const int32_t *rows, const int64_t *offsets,
                     int32_t *idx, int64_t n, int64_t capacity, const Status *st,
                     uint32_t *long_list, uint32_t *long_count, hipStream_t s);
@@ -314,9 +332,11 @@ struct EvalArgs {
     const int32_t *pair_of;        // [n_pt], < 0: point skipped
     const double *pos;             // [3][n_pt]
     double *acc, *pot;             // [3][n_pt], [n_pt] (pot may be null)
-    int32_t *bad;                  // count of pair_of >= n_pair
+    int64_t *bad;                  // (pinned host) set to 1 by a pair_of >= n_pair
 };
 void launch_tidal_eval(const EvalArgs &e, hipStream_t s);
+// *count (device, zeroed) = points with pair_of >= n_pair.
+void launch_tidal_bad(const EvalArgs &e, int64_t *count, hipStream_t s);
 // v += a dt over [3][n] (long-range kick).
 void launch_kick(double *vel, const double *acc, int64_t n, double dt, hipStream_t s);
 // Generalized inverse of the measure-point map at d_c = 1 (host memory,

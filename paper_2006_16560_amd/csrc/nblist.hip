@@ -15,6 +15,8 @@
 // overflowed, a walk of the near region per group (same opening rule)
 // replaces the hand-over; if the bounds ask for more scratch than the
 // caller allows, a counting pass gives exact bounds first.
+#include <cstddef>
+
 #include "launch.h"
 #include "walk.h"
 
@@ -178,8 +180,11 @@ __global__ __launch_bounds__(kThreads) void k_nb(TreeDev t, const uint32_t *grou
 // order) from a per-target cursor, which ends as the target's count (the
 // lists are sorted afterwards, so the slot order is irrelevant). Nothing is
 // written when the rows exceed the scratch (row_off[n] > row_cap): the
-// caller enlarges it and runs the passes again.
+// caller enlarges it and runs the passes again. (The pass waits for gathers;
+// with one wave per header it took as long as the longest list of leaves:
+// 37 us at a thousand stars, 68 us at 64k, now 15 and 47.)
 constexpr int kHitBuf = 8;
+constexpr int64_t kMaxParts = 16;
 
 struct NbRecLds {
     uint32_t start[kWave], pre[kWave];
@@ -219,7 +224,15 @@ __global__ __launch_bounds__(kThreads) void k_nb_rec(TreeDev t, NbRecords rec, c
     const int lane = lane_id();
     const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t r = wave0; r < nrec; r += nwaves) {
+    // with fewer headers than waves, a header's batches are shared by `parts`
+    // waves (the slots of a row are claimed, so any wave may test any batch)
+    const int64_t share = nwaves / (int64_t)(nrec ? nrec : 1u);
+    const uint32_t parts = share < 1 ? 1u : (share > kMaxParts ? (uint32_t)kMaxParts : (uint32_t)share);
+    const uint32_t bstep = parts * kWave;
+    for (int64_t rp = wave0; rp < (int64_t)nrec * parts; rp += nwaves) {
+        // (parts above 1 only with fewer headers than waves)
+        const int64_t r = parts == 1u ? rp : (int64_t)((uint32_t)rp / parts);
+        const uint32_t first = parts == 1u ? 0u : ((uint32_t)rp % parts) * kWave;
         const uint4 q = rec.head[r];
         const uint32_t gfirst = (uint32_t)uniform((int)q.x), gn = (uint32_t)uniform((int)q.y);
         const uint32_t loff = (uint32_t)uniform((int)q.z);
@@ -278,15 +291,15 @@ __global__ __launch_bounds__(kThreads) void k_nb_rec(TreeDev t, NbRecords rec, c
                     }
                 }
             };
-            gather(0);
-            for (uint32_t base = 0; base < total; base += kWave) {
+            if (first < total) gather(first);
+            for (uint32_t base = first; base < total; base += bstep) {
                 wave_sync();  // the previous batch has been read
                 if (base + lane < total) {
                     L.jp[lane] = pn;
                     L.jk[lane] = kn;
                 }
                 wave_sync();
-                if (base + kWave < total) gather(base + kWave);
+                if (base + bstep < total) gather(base + bstep);
                 const int m = (int)(total - base < (uint32_t)kWave ? total - base : (uint32_t)kWave);
                 if (act) {
                     const int step = S * 32;
@@ -607,20 +620,34 @@ void launch_nb_write(const TreeDev &t, const uint32_t *groups, Status *st, uint3
                        groups, st, cursor, row_off, rows, row_cap, spill, queue, rec);
 }
 
-__global__ void k_nb_summary(const int64_t *offsets, const int64_t *row_off, int64_t n,
-                             const uint32_t *rec_count, Status *st) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->nb_total = offsets[n];
-        st->nb_rows = row_off[n];
-        st->rec_used[0] = rec_count[0];
-        st->rec_used[1] = rec_count[1];
+// The status words to the host's copy (pinned), a word per lane; with lists,
+// their size, the rows' and the hand-over's use in place of the unset words.
+__global__ void k_status_out(const Status *st, const uint32_t *leaf_slots, const int64_t *offsets,
+                             const int64_t *row_off, int64_t n, const uint32_t *rec_count,
+                             Status *host) {
+    constexpr int kWords = (int)(sizeof(Status) / 8);
+    static_assert(sizeof(Status) % 8 == 0 && kWords <= kWave, "one word per lane");
+    const int l = threadIdx.x;
+    static_assert(kDeepSlots <= kWave, "one slot per lane");
+    const uint64_t leaves =
+        wave_sum((unsigned long long)(l < kDeepSlots ? leaf_slots[l * kDeepStride] : 0u));
+    if (l >= kWords) return;
+    uint64_t v = reinterpret_cast<const uint64_t *>(st)[l];
+    if (l == (int)(offsetof(Status, n_leaves) / 8)) v = leaves;
+    if (offsets) {
+        if (l == (int)(offsetof(Status, nb_total) / 8)) v = (uint64_t)offsets[n];
+        if (l == (int)(offsetof(Status, nb_rows) / 8)) v = (uint64_t)row_off[n];
+        if (l == (int)(offsetof(Status, rec_used) / 8))
+            v = *reinterpret_cast<const uint64_t *>(rec_count);
     }
+    reinterpret_cast<uint64_t *>(host)[l] = v;
 }
 
-void launch_nb_summary(const int64_t *offsets, const int64_t *row_off, int64_t n,
-                       const uint32_t *rec_count, Status *st, hipStream_t s) {
-    hipLaunchKernelGGL(k_nb_summary, dim3(1), dim3(kWave), 0, s, offsets, row_off, n, rec_count,
-                       st);
+void launch_status_out(const Status *st, const uint32_t *leaf_slots, const int64_t *offsets,
+                       const int64_t *row_off, int64_t n, const uint32_t *rec_count, Status *host,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_status_out, dim3(1), dim3(kWave), 0, s, st, leaf_slots, offsets, row_off,
+                       n, rec_count, host);
 }
 
 void launch_nb_sort(const int64_t *row_off, const int32_t *rows, const int64_t *offsets,
@@ -631,8 +658,10 @@ void launch_nb_sort(const int64_t *row_off, const int32_t *rows, const int64_t *
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_nb_sort_short, dim3((unsigned)blocks), dim3(kThreads), 0, s, row_off,
                        rows, offsets, idx, n, capacity, st, long_list, long_count);
-    hipLaunchKernelGGL(k_nb_sort_long, dim3(1024), dim3(kThreads), 0, s, offsets, idx, n, capacity,
-                       st, (const uint32_t *)long_list, (const uint32_t *)long_count);
+    const int64_t lb = (n + kWave - 1) / kWave;
+    hipLaunchKernelGGL(k_nb_sort_long, dim3((unsigned)(lb < 1024 ? lb : 1024)), dim3(kThreads), 0,
+                       s, offsets, idx, n, capacity, st, (const uint32_t *)long_list,
+                       (const uint32_t *)long_count);
 }
 
 }  // namespace petar

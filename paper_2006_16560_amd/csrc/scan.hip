@@ -1,6 +1,11 @@
-// Exclusive prefix sums (three passes: block totals, scan of the totals,
-// block-local scan plus offset) and fill kernels. Deterministic: integer
-// sums in a fixed order.
+// Exclusive prefix sums and fill kernels. Deterministic: integer sums in a
+// fixed order.
+//
+// A launch costs 5 to 10 us on its own, more than a small scan's work, so the
+// scan takes as few as its size allows: one block (up to kOneBlockTiles tiles
+// in turn); block totals, then a scan in which every block adds up the totals
+// before it (up to kSelfTotals, 10 KB a block at ten million counts); above
+// that, a third launch scans the totals between the two.
 #include "launch.h"
 
 namespace petar {
@@ -10,15 +15,19 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kOneThreads = 1024;
+constexpr int kOneBlockTiles = 4;   // of 4096 counts
+constexpr int64_t kSelfTotals = 4096;
 
+template <int Threads = kScanThreads>
 __device__ int64_t block_excl_scan(int64_t v, int64_t *total) {
-    __shared__ int64_t wsum[kScanThreads / kWave];
+    __shared__ int64_t wsum[Threads / kWave];
     int64_t incl = wave_incl_scan(v);
     int w = threadIdx.x / kWave;
     if (lane_id() == kWave - 1) wsum[w] = incl;
     __syncthreads();
     int64_t off = 0, tot = 0;
-    for (int k = 0; k < kScanThreads / kWave; k++) {
+    for (int k = 0; k < Threads / kWave; k++) {
         if (k < w) off += wsum[k];
         tot += wsum[k];
     }
@@ -55,9 +64,20 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_totals(int64_t *bsum, int
     if (threadIdx.x == 0) bsum[nb] = carry;
 }
 
-template <typename In, typename Out>
-__global__ __launch_bounds__(kScanThreads) void k_block_scan(const In *in, Out *out, int64_t n,
+// Block-local scan plus the sum of the earlier blocks: bsum holds the
+// totals, added up here (kSelf), or already their prefix sums. kClear: the
+// counts are set to 0 once read.
+template <typename In, typename Out, bool kSelf, bool kClear>
+__global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, int64_t n,
                                                              const int64_t *bsum, int64_t nb) {
+    int64_t before = 0;
+    if constexpr (kSelf) {
+        int64_t part = 0;
+        for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += kScanThreads) part += bsum[k];
+        block_excl_scan(part, &before);
+    } else {
+        before = bsum[blockIdx.x];
+    }
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int64_t vals[kScanItems];
     int64_t s = 0;
@@ -67,15 +87,48 @@ __global__ __launch_bounds__(kScanThreads) void k_block_scan(const In *in, Out *
         vals[k] = i < n ? (int64_t)in[i] : 0;
         s += vals[k];
     }
+    if constexpr (kClear) {
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++)
+            if (base + k < n) in[base + k] = 0;
+    }
     int64_t tot;
-    int64_t off = block_excl_scan(s, &tot) + bsum[blockIdx.x];
+    int64_t off = block_excl_scan(s, &tot) + before;
 #pragma unroll
     for (int k = 0; k < kScanItems; k++) {
         int64_t i = base + k;
         if (i < n) out[i] = (Out)off;
         off += vals[k];
     }
-    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = (Out)bsum[nb];
+    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = (Out)(before + tot);
+}
+
+// The whole scan by one block, kOneThreads * Items counts at a time.
+template <typename In, typename Out, bool kClear>
+__global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int64_t n) {
+    constexpr int Items = 4;
+    int64_t carry = 0;
+    for (int64_t c = 0; c < n; c += (int64_t)kOneThreads * Items) {
+        const int64_t base = c + (int64_t)threadIdx.x * Items;
+        int64_t vals[Items], s = 0;
+#pragma unroll
+        for (int k = 0; k < Items; k++) {
+            vals[k] = base + k < n ? (int64_t)in[base + k] : 0;
+            s += vals[k];
+        }
+        int64_t tot;
+        int64_t off = carry + block_excl_scan<kOneThreads>(s, &tot);
+#pragma unroll
+        for (int k = 0; k < Items; k++) {
+            if (base + k < n) {
+                out[base + k] = (Out)off;
+                if constexpr (kClear) in[base + k] = 0;
+            }
+            off += vals[k];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) out[n] = (Out)carry;
 }
 
 template <typename T>
@@ -85,14 +138,42 @@ __global__ void k_fill(T *p, T v, int64_t n) {
         p[i] = v;
 }
 
-template <typename In, typename Out>
-void scan_impl(const In *in, Out *out, int64_t n, int64_t *ws, hipStream_t s) {
+// Several buffers set to 0 in one launch (a row of blocks each).
+struct FillList {
+    uint32_t *p[kFillPieces];
+    int64_t words[kFillPieces];
+    int n;
+};
+__global__ void k_fill_words(FillList l) {
+    uint32_t *p = l.p[blockIdx.y];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < l.words[blockIdx.y];
+         i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = 0u;
+}
+
+__global__ void k_words_out(const int64_t *words, int n, int64_t *host) {
+    if ((int)threadIdx.x < n) host[threadIdx.x] = words[threadIdx.x];
+}
+
+template <typename In, typename Out, bool kClear>
+void scan_impl(In *in, Out *out, int64_t n, int64_t *ws, hipStream_t s) {
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(k_block_totals<In>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, ws);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kScanThreads), 0, s, ws, nb);
-    hipLaunchKernelGGL((k_block_scan<In, Out>), dim3((unsigned)nb), dim3(kScanThreads), 0, s, in,
-                       out, n, (const int64_t *)ws, nb);
+    if (nb <= kOneBlockTiles) {
+        hipLaunchKernelGGL((k_scan_one<In, Out, kClear>), dim3(1), dim3(kOneThreads), 0, s, in,
+                           out, n);
+        return;
+    }
+    const dim3 g((unsigned)nb), b(kScanThreads);
+    hipLaunchKernelGGL(k_block_totals<In>, g, b, 0, s, (const In *)in, n, ws);
+    if (nb <= kSelfTotals) {
+        hipLaunchKernelGGL((k_block_scan<In, Out, true, kClear>), g, b, 0, s, in, out, n,
+                           (const int64_t *)ws, nb);
+        return;
+    }
+    hipLaunchKernelGGL(k_scan_totals, dim3(1), b, 0, s, ws, nb);
+    hipLaunchKernelGGL((k_block_scan<In, Out, false, kClear>), g, b, 0, s, in, out, n,
+                       (const int64_t *)ws, nb);
 }
 
 template <typename T>
@@ -108,12 +189,31 @@ void fill_impl(T *p, T v, int64_t n, hipStream_t s) {
 int64_t scan_ws_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
 
 void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl(in, out, n, ws, s);
+    scan_impl<uint32_t, int64_t, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+}
+void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
+    scan_impl<uint32_t, int64_t, true>(in, out, n, ws, s);
 }
 void scan_u32_to_u32(const uint32_t *in, uint32_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl(in, out, n, ws, s);
+    scan_impl<uint32_t, uint32_t, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+}
+void fill_words(std::initializer_list<FillWords> pieces, hipStream_t s) {
+    FillList l{};
+    unsigned most = 1;
+    for (const FillWords &p : pieces) {
+        l.p[l.n] = p.p;
+        l.words[l.n++] = p.words;
+        const unsigned blocks = (unsigned)((p.words + 255) / 256);
+        most = blocks > most ? blocks : most;
+    }
+    hipLaunchKernelGGL(k_fill_words, dim3(most > 256 ? 256 : most, (unsigned)l.n), dim3(256), 0, s,
+                       l);
 }
 void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) { fill_impl(p, v, n, s); }
 void fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s) { fill_impl(p, v, n, s); }
+
+void words_out(const int64_t *words, int n, int64_t *host, hipStream_t s) {
+    hipLaunchKernelGGL(k_words_out, dim3(1), dim3(kWave), 0, s, words, n, host);
+}
 
 }  // namespace petar

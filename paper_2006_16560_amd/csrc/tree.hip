@@ -11,6 +11,8 @@
 // leaf; otherwise its non-empty octants are its children. Cells carry mass,
 // centre of mass, second moment about it (giving the traceless quadrupole of
 // eq. quadtr), particle bounding box and max search radius.
+#include <utility>
+
 #include "launch.h"
 
 namespace petar {
@@ -27,82 +29,125 @@ inline unsigned grid_for(int64_t n, int threads = kThreads, int64_t cap = 65535)
 }
 
 // ------------------------------------------------------------------ bbox
+// Extent and validity of the particles: block partials and one block per
+// system that finishes them; a single block (few particles) writes the root
+// cube itself. (Finished by the last block to arrive, counted with
+// agent-scope acquire and release, a launch of a thousand blocks took 33
+// instead of 17 us: each release writes back the XCD's L2.)
 constexpr int kBBoxBlocks = 1024;
 
-__global__ __launch_bounds__(kThreads) void k_bbox_partial(const double *pos, const double *mass,
-                                                           int64_t n, double *part, RootBox *rb) {
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    int bad = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+struct Extent {
+    double lo[3], hi[3];
+    __device__ __forceinline__ void clear() {
         for (int d = 0; d < 3; d++) {
-            double x = pos[(int64_t)d * n + i];
-            if (!isfinite(x)) bad = 1;
-            lo[d] = fmin(lo[d], x);
-            hi[d] = fmax(hi[d], x);
+            lo[d] = INFINITY;
+            hi[d] = -INFINITY;
         }
-        double m = mass[i];
-        if (!isfinite(m) || m < 0.0) bad = 1;
     }
-    __shared__ double sh[kThreads / kWave][6];
-    int w = threadIdx.x / kWave;
+    // One particle (x, y, z, m); whether its data are invalid.
+    __device__ __forceinline__ int take(const double p[4]) {
+        int bad = 0;
+        for (int d = 0; d < 3; d++) {
+            if (!isfinite(p[d])) bad = 1;
+            lo[d] = fmin(lo[d], p[d]);
+            hi[d] = fmax(hi[d], p[d]);
+        }
+        if (!isfinite(p[3]) || p[3] < 0.0) bad = 1;
+        return bad;
+    }
+    // The block's extent in thread 0.
+    __device__ void reduce_block() {
+        __shared__ double sh[kThreads / kWave][6];
+        const int w = threadIdx.x / kWave;
+        for (int d = 0; d < 3; d++) {
+            const double a = wave_min(lo[d]), b = wave_max(hi[d]);
+            if (lane_id() == 0) {
+                sh[w][d] = a;
+                sh[w][3 + d] = b;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int d = 0; d < 3; d++) {
+                lo[d] = sh[0][d];
+                hi[d] = sh[0][3 + d];
+                for (int k = 1; k < kThreads / kWave; k++) {
+                    lo[d] = fmin(lo[d], sh[k][d]);
+                    hi[d] = fmax(hi[d], sh[k][3 + d]);
+                }
+            }
+        }
+    }
+};
+
+__device__ __forceinline__ void write_root(RootBox *rb, const Extent &e, double cells) {
+#pragma clang fp contract(off)
+    double ext = 0.0;
     for (int d = 0; d < 3; d++) {
-        double a = wave_min(lo[d]), b = wave_max(hi[d]);
-        if (lane_id() == 0) {
-            sh[w][d] = a;
-            sh[w][3 + d] = b;
+        const double x = e.hi[d] - e.lo[d];
+        if (x > ext) ext = x;
+    }
+    if (!(ext > 0.0)) ext = 1.0;
+    for (int d = 0; d < 3; d++) rb->lo[d] = e.lo[d];
+    rb->ext = ext;
+    rb->scale = cells / ext;
+}
+
+// Block (b, s) of (nblk, n_sys): its share of the particles of system s
+// ([off[s], off[s + 1]), all n without off); rb[s] and part[s nblk ..] are the
+// system's, bad input is counted in rb[0].
+__global__ __launch_bounds__(kThreads) void k_bbox_partial(const double *pos, const double *mass,
+                                                           int64_t n, const int64_t *off,
+                                                           double *part, RootBox *rb,
+                                                           double cells) {
+    const int s = blockIdx.y, nblk = gridDim.x;
+    const int64_t beg = off ? off[s] : 0, end = off ? off[s + 1] : n;
+    Extent e;
+    e.clear();
+    int bad = 0;
+    const int64_t step = (int64_t)nblk * kThreads;
+    int64_t i = beg + (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    for (; i + 3 * step < end; i += 4 * step) {  // 16 loads in flight
+        double x[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+#pragma unroll
+            for (int d = 0; d < 3; d++) x[q][d] = pos[(int64_t)d * n + i + q * step];
+            x[q][3] = mass[i + q * step];
         }
+#pragma unroll
+        for (int q = 0; q < 4; q++) bad |= e.take(x[q]);
     }
-    if (__ballot(bad)) {
-        if (lane_id() == 0) atomicAdd(&rb->bad, 1);
+    for (; i < end; i += step) {
+        const double x[4] = {pos[i], pos[n + i], pos[2 * n + i], mass[i]};
+        bad |= e.take(x);
     }
-    __syncthreads();
-    if (threadIdx.x < 6) {
-        double v = sh[0][threadIdx.x];
-        for (int k = 1; k < kThreads / kWave; k++)
-            v = threadIdx.x < 3 ? fmin(v, sh[k][threadIdx.x]) : fmax(v, sh[k][threadIdx.x]);
-        part[blockIdx.x * 6 + threadIdx.x] = v;
+    if (__ballot(bad) && lane_id() == 0) atomicAdd(&rb[0].bad, 1);
+    e.reduce_block();
+    if (threadIdx.x != 0) return;
+    if (nblk == 1) {
+        write_root(&rb[s], e, cells);
+        return;
+    }
+    part += ((int64_t)s * nblk + blockIdx.x) * 6;
+    for (int d = 0; d < 3; d++) {
+        part[d] = e.lo[d];
+        part[3 + d] = e.hi[d];
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_bbox_final(const double *part, int nblk, RootBox *rb) {
-#pragma clang fp contract(off)
-    __shared__ double sh[kThreads / kWave][6];
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x)
+__global__ __launch_bounds__(kThreads) void k_bbox_final(const double *part, int nblk, RootBox *rb,
+                                                         double cells) {
+    part += (int64_t)blockIdx.x * nblk * 6;
+    Extent e;
+    e.clear();
+    for (int b = threadIdx.x; b < nblk; b += kThreads)
         for (int d = 0; d < 3; d++) {
-            lo[d] = fmin(lo[d], part[b * 6 + d]);
-            hi[d] = fmax(hi[d], part[b * 6 + 3 + d]);
+            e.lo[d] = fmin(e.lo[d], part[b * 6 + d]);
+            e.hi[d] = fmax(e.hi[d], part[b * 6 + 3 + d]);
         }
-    int w = threadIdx.x / kWave;
-    for (int d = 0; d < 3; d++) {
-        double a = wave_min(lo[d]), b = wave_max(hi[d]);
-        if (lane_id() == 0) {
-            sh[w][d] = a;
-            sh[w][3 + d] = b;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double l[3], h[3];
-        for (int d = 0; d < 3; d++) {
-            l[d] = sh[0][d];
-            h[d] = sh[0][3 + d];
-            for (int k = 1; k < kThreads / kWave; k++) {
-                l[d] = fmin(l[d], sh[k][d]);
-                h[d] = fmax(h[d], sh[k][3 + d]);
-            }
-        }
-        double ext = 0.0;
-        for (int d = 0; d < 3; d++) {
-            double e = h[d] - l[d];
-            if (e > ext) ext = e;
-        }
-        if (!(ext > 0.0)) ext = 1.0;
-        for (int d = 0; d < 3; d++) rb->lo[d] = l[d];
-        rb->ext = ext;
-        rb->scale = 2097152.0 / ext;
-    }
+    e.reduce_block();
+    if (threadIdx.x == 0) write_root(&rb[blockIdx.x], e, cells);
 }
 
 // ------------------------------------------------------------------ keys
@@ -123,59 +168,8 @@ __global__ __launch_bounds__(kThreads) void k_keys(const double *pos, int64_t n,
     }
 }
 
-// Batched mode: each system gets its own root cube (one block per system)
-// and keys with the system id above kBatchLevels octal digits.
-__global__ __launch_bounds__(kThreads) void k_bbox_systems(const double *pos, const double *mass,
-                                                           int64_t n, const int64_t *off,
-                                                           RootBox *rb) {
-#pragma clang fp contract(off)
-    const int s = blockIdx.x;
-    const int64_t beg = off[s], end = off[s + 1];
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    int bad = 0;
-    for (int64_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
-        for (int d = 0; d < 3; d++) {
-            double x = pos[(int64_t)d * n + i];
-            if (!isfinite(x)) bad = 1;
-            lo[d] = fmin(lo[d], x);
-            hi[d] = fmax(hi[d], x);
-        }
-        double m = mass[i];
-        if (!isfinite(m) || m < 0.0) bad = 1;
-    }
-    __shared__ double sh[kThreads / kWave][6];
-    const int w = threadIdx.x / kWave;
-    for (int d = 0; d < 3; d++) {
-        double a = wave_min(lo[d]), b = wave_max(hi[d]);
-        if (lane_id() == 0) {
-            sh[w][d] = a;
-            sh[w][3 + d] = b;
-        }
-    }
-    if (__ballot(bad) && lane_id() == 0) atomicAdd(&rb[0].bad, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double l[3], h[3];
-        for (int d = 0; d < 3; d++) {
-            l[d] = sh[0][d];
-            h[d] = sh[0][3 + d];
-            for (int k = 1; k < kThreads / kWave; k++) {
-                l[d] = fmin(l[d], sh[k][d]);
-                h[d] = fmax(h[d], sh[k][3 + d]);
-            }
-        }
-        double ext = 0.0;
-        for (int d = 0; d < 3; d++) {
-            double e = h[d] - l[d];
-            if (e > ext) ext = e;
-        }
-        if (!(ext > 0.0)) ext = 1.0;
-        for (int d = 0; d < 3; d++) rb[s].lo[d] = end > beg ? l[d] : 0.0;
-        rb[s].ext = ext;
-        rb[s].scale = ldexp(1.0, kBatchLevels) / ext;
-    }
-}
-
+// Batched mode: each system has its own root cube, and keys carry the system
+// id above kBatchLevels octal digits.
 __global__ __launch_bounds__(kThreads) void k_keys_systems(const double *pos, int64_t n,
                                                            const int64_t *off, int n_sys,
                                                            const RootBox *rb, uint64_t *key,
@@ -214,7 +208,10 @@ __global__ __launch_bounds__(kThreads) void k_keys_systems(const double *pos, in
 constexpr int kSortRounds = 8;
 constexpr int kSortTile = kThreads * kSortRounds;  // 2048 keys
 constexpr int kRadix = 256;
+constexpr int64_t kFewTiles = 64;
 
+// hist[digit][tile] (kFew: hist[tile][digit])
+template <bool kFew>
 __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint64_t *key, int64_t n, int shift,
                                                         uint32_t *hist, int64_t ntiles,
                                                         const int64_t *n_dev) {
@@ -228,7 +225,10 @@ __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint64_t *key, int
         if (k < n) atomicAdd(&cnt[(key[k] >> shift) & 255], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
+    if constexpr (kFew)
+        hist[(int64_t)blockIdx.x * kRadix + threadIdx.x] = cnt[threadIdx.x];
+    else
+        hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
 // Block d: exclusive prefix of digit d's tile counts over the tiles, and the
@@ -270,6 +270,26 @@ __global__ __launch_bounds__(kThreads) void k_sort_rowscan(const uint32_t *hist,
     if (t == 0) dtot[blockIdx.x] = carry;
 }
 
+// The rank of lane's digit among the wave's keys so far: its running count
+// in cnt plus the matching lanes below (8 ballots).
+__device__ __forceinline__ uint32_t digit_rank(uint32_t *cnt, int d, bool valid) {
+    unsigned long long m = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; b++) {
+        const unsigned long long bb = __ballot((d >> b) & 1);
+        m &= ((d >> b) & 1) ? bb : ~bb;
+    }
+    const int wrank = lanes_below(m);
+    const uint32_t before = valid ? cnt[d] : 0u;
+    wave_sync();  // every lane has read its digit's count
+    if (valid && wrank == 0) cnt[d] = before + (uint32_t)__popcll(m);
+    wave_sync();
+    return before + (uint32_t)wrank;
+}
+
+// kFew: every block adds up the counts of the earlier tiles itself (no scan
+// launch; up to kFewTiles tiles, 64 KB read per block).
+template <bool kFew>
 __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_in,
                                                            const uint32_t *val_in,
                                                            uint64_t *key_out, uint32_t *val_out,
@@ -292,7 +312,26 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
     // exclusive scans over the digits of this tile's counts and of the
     // digit totals; a key at tile position p with digit d goes to
     // gbase[d] + p (modulo 2^32; the true position is below n)
-    const uint32_t c = hist[(int64_t)t * ntiles + tile], dt = dtot[t];
+    uint32_t c, dt, earlier;
+    if constexpr (kFew) {
+        c = hist[tile * kRadix + t];
+        dt = earlier = 0;
+        for (int i0 = 0; i0 < (int)ntiles; i0 += 16) {  // 16 loads in flight
+            uint32_t v[16];
+#pragma unroll
+            for (int q = 0; q < 16; q++)
+                v[q] = i0 + q < (int)ntiles ? hist[(i0 + q) * kRadix + t] : 0u;
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                dt += v[q];
+                earlier += i0 + q < (int)tile ? v[q] : 0u;
+            }
+        }
+    } else {
+        c = hist[(int64_t)t * ntiles + tile];
+        dt = dtot[t];
+        earlier = offs[(int64_t)t * ntiles + tile];
+    }
     const uint32_t incl = wave_incl_scan(c), incl_d = wave_incl_scan(dt);
     if (lane_id() == kWave - 1) {
         wsum[w] = incl;
@@ -306,7 +345,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
         off_d += wsum_d[k];
     }
     tile_start[t] = off + incl - c;
-    gbase[t] = (off_d + incl_d - dt) + offs[(int64_t)t * ntiles + tile] - (off + incl - c);
+    gbase[t] = (off_d + incl_d - dt) + earlier - (off + incl - c);
     // Each wave ranks its own quarter of the tile, kSortRounds keys per lane
     // in order: a key's rank among the wave's earlier keys of its digit is
     // the wave's running count plus the matching lanes below it (8 ballots).
@@ -321,18 +360,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
         kk[r] = valid ? key_in[k] : 0;
         vv[r] = valid ? val_in[k] : 0;
         const int d = (int)((kk[r] >> shift) & 255);
-        unsigned long long m = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; b++) {
-            const unsigned long long bb = __ballot((d >> b) & 1);
-            m &= ((d >> b) & 1) ? bb : ~bb;
-        }
-        const int wrank = lanes_below(m);
-        const uint32_t before = valid ? cnt[d] : 0u;
-        wave_sync();  // every lane has read its digit's count
-        rk[r] = before + (uint32_t)wrank;
-        if (valid && wrank == 0) cnt[d] = before + (uint32_t)__popcll(m);
-        wave_sync();
+        rk[r] = digit_rank(cnt, d, valid);
     }
     __syncthreads();
     // wave offsets of digit t: the counts of the earlier waves
@@ -366,6 +394,92 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
     }
 }
 
+// The whole sort by one block, every pass in LDS: Per keys a thread in
+// registers, ranked wave by wave as in k_sort_scatter. A pass in which all
+// keys have one digit moves nothing. Four thousand keys, 8 passes: 32 us
+// instead of 24 launches (170 us with their gaps in a captured graph).
+constexpr int kOneThreads = 1024;
+constexpr int kOneWaves = kOneThreads / kWave;
+
+template <int Per>
+__global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint64_t *key_in,
+                                                          const uint32_t *val_in,
+                                                          uint64_t *key_out, uint32_t *val_out,
+                                                          int64_t n, int passes,
+                                                          const int64_t *n_dev) {
+    __shared__ uint64_t sk[kOneThreads * Per];
+    __shared__ uint32_t sv[kOneThreads * Per];
+    __shared__ uint32_t cnt[kOneWaves][kRadix];
+    __shared__ uint32_t wsum[kRadix / kWave];
+    __shared__ int one_digit[2];  // by the parity of the pass
+    if (n_dev) n = *n_dev;
+    const int t = threadIdx.x, w = t / kWave;
+    const int pos0 = w * kWave * Per + lane_id();  // + r kWave
+    uint64_t kk[Per];
+    uint32_t vv[Per], rk[Per];
+#pragma unroll
+    for (int r = 0; r < Per; r++) {
+        const int k = pos0 + r * kWave;
+        kk[r] = k < n ? key_in[k] : 0;
+        vv[r] = k < n ? val_in[k] : 0;
+    }
+    for (int pass = 0; pass < passes; pass++) {
+        const int shift = 8 * pass;
+        for (int i = t; i < kOneWaves * kRadix; i += kOneThreads) (&cnt[0][0])[i] = 0u;
+        if (t == 0) one_digit[pass & 1] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < Per; r++)
+            rk[r] = digit_rank(cnt[w], (int)((kk[r] >> shift) & 255), pos0 + r * kWave < n);
+        __syncthreads();
+        // digit t: counts of the earlier waves, then of the smaller digits
+        uint32_t tot = 0, incl = 0;
+        if (t < kRadix) {
+            for (int q = 0; q < kOneWaves; q++) {
+                const uint32_t v = cnt[q][t];
+                cnt[q][t] = tot;
+                tot += v;
+            }
+            if (tot == (uint32_t)n) one_digit[pass & 1] = 1;
+            incl = wave_incl_scan(tot);
+            if (lane_id() == kWave - 1) wsum[w] = incl;
+        }
+        __syncthreads();
+        if (one_digit[pass & 1]) continue;  // the same for the whole block
+        if (t < kRadix) {
+            uint32_t first = incl - tot;
+            for (int q = 0; q < w; q++) first += wsum[q];
+            for (int q = 0; q < kOneWaves; q++) cnt[q][t] += first;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < Per; r++) {
+            if (pos0 + r * kWave < n) {
+                const uint32_t p = cnt[w][(kk[r] >> shift) & 255] + rk[r];
+                sk[p] = kk[r];
+                sv[p] = vv[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < Per; r++) {
+            const int k = pos0 + r * kWave;
+            if (k < n) {
+                kk[r] = sk[k];
+                vv[r] = sv[k];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < Per; r++) {
+        const int k = pos0 + r * kWave;
+        if (k < n) {
+            key_out[k] = kk[r];
+            val_out[k] = vv[r];
+        }
+    }
+}
+
 // ------------------------------------------------------------ gathers
 // orig[k] = input index of the k-th particle in Morton order; rank is its
 // inverse. The particle data are then moved with coalesced reads in input
@@ -388,6 +502,22 @@ __global__ __launch_bounds__(kThreads) void k_scatter_particles(const double *po
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         ps[rank[i]] = make_double4(pos[i], pos[n + i], pos[2 * n + i], mass[i]);
+}
+
+// Both at once, by gathers: up to kGatherMax particles (16 MB of input) the
+// scattered reads come from the caches and a launch is saved.
+constexpr int64_t kGatherMax = 1 << 18;
+__global__ __launch_bounds__(kThreads) void k_gather_all(const double *pos, const double *mass,
+                                                         const uint32_t *idx, int64_t n,
+                                                         double4 *ps, uint32_t *orig,
+                                                         uint32_t *rank) {
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
+         k += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t o = idx[k];
+        orig[k] = o;
+        rank[o] = (uint32_t)k;
+        ps[k] = make_double4(pos[o], pos[n + o], pos[2 * n + o], mass[o]);
+    }
 }
 
 // ------------------------------------------------------------ octree
@@ -538,16 +668,27 @@ __global__ __launch_bounds__(kThreads) void k_octree_count(const uint64_t *key, 
 // keys), so that no thread walks a whole root-to-leaf chain of searches.
 __global__ __launch_bounds__(kThreads) void k_octree_emit(const uint64_t *key, int64_t n,
                                                           int levels, const int64_t *base,
-                                                          PreOrder pre, const Status *st) {
-    if (st->cell_overflow) return;
+                                                          PreOrder pre, int64_t node_cap,
+                                                          Status *st) {
+    // device cell count for the build's second half: the scanned count, or 0
+    // (with Status::cell_overflow raised) when it exceeds the arrays'
+    // capacity, so that every later kernel does nothing
+    const int64_t cells = base[n];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->n_nodes = cells > node_cap ? 0 : cells;
+        if (cells > node_cap) st->cell_overflow = 1;
+    }
+    if (cells > node_cap) return;
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b = base[k];
         const int64_t nemit = base[k + 1] - b;
         if (nemit == 0) continue;
         const int l0 = first_level(key, k, levels);
-        for (int u = 0; u < nemit; u++)
+        for (int u = 0; u < nemit; u++) {
             pre.info[b + u] = make_uint4((uint32_t)k, 0u, (uint32_t)(l0 + u) << 1, 0u);
+            pre.nchild[b + u] = 0u;
+        }
     }
 }
 
@@ -598,14 +739,11 @@ __global__ __launch_bounds__(kThreads) void k_octree_write(const uint64_t *key, 
     }
 }
 
-// Device cell count for the build's second half: the scanned count, or 0
-// (with Status::cell_overflow raised) when it exceeds the arrays' capacity,
-// so that every later kernel does nothing.
-// What the host needs after the first half of an eager build, gathered into
-// the status words so that one copy reads it: the cell count, the input
-// check of the root box and the deepest cell level.
+// What the host needs after the first half of an eager build, written to its
+// (pinned) words: the cell count, the input check of the root box and the
+// deepest cell level.
 __global__ void k_build_head(const int64_t *base, int64_t n, const RootBox *rb,
-                             const uint32_t *deep_slots, Status *st) {
+                             const uint32_t *deep_slots, int64_t *host) {
     if (blockIdx.x != 0) return;
     uint32_t d = 0;
     for (int w = threadIdx.x; w < kDeepSlots; w += blockDim.x) {
@@ -617,39 +755,46 @@ __global__ void k_build_head(const int64_t *base, int64_t n, const RootBox *rb,
         d = u > d ? u : d;
     }
     if (threadIdx.x == 0) {
-        st->cells = base[n];
-        st->bad_input = rb->bad;
-        st->deep = d;
-    }
-}
-
-__global__ void k_cell_count(const int64_t *base, int64_t n, int64_t node_cap, Status *st) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        int64_t c = base[n];
-        if (c > node_cap) {
-            st->cell_overflow = 1;
-            c = 0;
-        }
-        st->n_nodes = c;
+        host[0] = base[n];
+        host[1] = rb->bad;
+        host[2] = d;
     }
 }
 
 // perm[new] = old after the stable sort by level; its inverse.
-__global__ __launch_bounds__(kThreads) void k_invert(const uint32_t *perm, const int64_t *n_dev,
-                                                     uint32_t *new_of_old) {
+// Also level_off[l] = first cell of level >= l (levels above the deepest one
+// get n_nodes), by searches over the sorted levels.
+__global__ __launch_bounds__(kThreads) void k_invert(const uint32_t *perm, const uint64_t *lkey,
+                                                     const int64_t *n_dev, uint32_t *new_of_old,
+                                                     uint32_t *level_off) {
     const int64_t n_nodes = *n_dev;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_nodes;
          i += (int64_t)gridDim.x * blockDim.x)
         new_of_old[perm[i]] = (uint32_t)i;
+    const int l = (int)threadIdx.x;
+    if (blockIdx.x != gridDim.x - 1 || l > kMaxLevel + 1) return;
+    int64_t lo = 0, hi = n_nodes;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if ((int64_t)lkey[mid] < l)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    level_off[l] = (uint32_t)lo;
 }
 
 // Level-order cell records. Sorting the pre-order cells stably by level keeps
 // each level in Morton order, so siblings are contiguous and the first child
-// of a cell is the cell that follows it in pre-order.
+// of a cell is the cell that follows it in pre-order. Also the deepest level
+// and, spread over kDeepSlots words, the number of leaves.
 __global__ __launch_bounds__(kThreads) void k_relayout(const uint32_t *perm, PreOrder pre,
                                                        const RootBox *rb, const uint64_t *key,
-                                                       int levels, TreeDev t) {
+                                                       int levels, TreeDev t, Status *st,
+                                                       uint32_t *leaf_slots) {
+    __shared__ uint32_t sh[kThreads / kWave];
     const int64_t n_nodes = *t.n_nodes_dev;
+    uint32_t leaves = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_nodes;
          i += (int64_t)gridDim.x * blockDim.x) {
         uint32_t old = perm[i];
@@ -661,22 +806,17 @@ __global__ __launch_bounds__(kThreads) void k_relayout(const uint32_t *perm, Pre
         t.nd_parent[i] = par == kNone ? kNone : pre.new_of_old[par];
         const uint64_t sys = key[in.x] >> (3 * levels);
         t.nd_hi[i].w = ldexp(rb[sys].ext, -info_level(in.z));
+        leaves += in.z & kLeafFlag;
+        if (i == n_nodes - 1) st->max_level = info_level(in.z);
     }
-}
-
-// level_off[l] = first cell of level >= l (cells are sorted by level).
-__global__ void k_level_offsets(TreeDev t, uint32_t *level_off) {
-    int l = threadIdx.x;
-    if (l > kMaxLevel + 1) return;  // levels above the deepest one get n_nodes
-    int64_t lo = 0, hi = *t.n_nodes_dev;
-    while (lo < hi) {
-        int64_t mid = (lo + hi) / 2;
-        if (info_level(t.nd_info[mid].z) < l)
-            lo = mid + 1;
-        else
-            hi = mid;
+    leaves = wave_sum(leaves);
+    if (lane_id() == 0) sh[threadIdx.x / kWave] = leaves;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t b = 0;
+        for (int w = 0; w < kThreads / kWave; w++) b += sh[w];
+        if (b) atomicAdd(&leaf_slots[(blockIdx.x % kDeepSlots) * kDeepStride], b);
     }
-    level_off[l] = (uint32_t)lo;
 }
 
 // Cell data of cell c. Leaves sum their particles (two passes: centre of
@@ -821,27 +961,31 @@ __global__ __launch_bounds__(kThreads) void k_moments_level(TreeDev t, int level
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_tree_summary(TreeDev t, Status *st) {
-    __shared__ uint32_t sh[kThreads / kWave];
-    const int64_t n_nodes = *t.n_nodes_dev;
-    uint32_t leaves = 0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_nodes;
-         c += (int64_t)gridDim.x * blockDim.x)
-        leaves += t.nd_info[c].z & kLeafFlag;
-    leaves = wave_sum(leaves);
-    if (lane_id() == 0) sh[threadIdx.x / kWave] = leaves;
+// Levels from..0 by one block, each after the one below it is written (the
+// block's waves share their L1, so a barrier is enough). The levels of a
+// small tree, and of any tree the few at the top, cost 2 to 3 us each here
+// and 6 to 9 us as launches.
+constexpr int kTopThreads = 512;       // 8 children of a cell in registers
+constexpr int64_t kSmallTree = 16384;  // cells
+__global__ __launch_bounds__(kTopThreads) void k_moments_top(TreeDev t, int from) {
+    __shared__ uint32_t off[kMaxLevel + 2];
+    if (threadIdx.x < kMaxLevel + 2) off[threadIdx.x] = t.level_off[threadIdx.x];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t b = 0;
-        for (int w = 0; w < kThreads / kWave; w++) b += sh[w];
-        if (b) atomicAdd((unsigned long long *)&st->n_leaves, (unsigned long long)b);
-        if (blockIdx.x == 0 && n_nodes > 0) st->max_level = info_level(t.nd_info[n_nodes - 1].z);
+    for (int l = from; l >= 0; l--) {
+        const uint32_t beg = off[l], end = off[l + 1];
+        if (beg == end) continue;
+        for (int64_t c = (int64_t)beg + threadIdx.x; c < (int64_t)end; c += kTopThreads) {
+            const uint4 info = t.nd_info[c];
+            if (!(info.z & kLeafFlag)) cell_moments<false>(t, (uint32_t)c, info);
+        }
+        __syncthreads();
     }
 }
 
 // ------------------------------------------------------- force preparation
 // Radii into Morton order (coalesced reads, scattered writes), with the
-// validity check 0 <= r_in < r_out <= r_search (all finite).
+// validity check 0 <= r_in < r_out <= r_search (all finite); and the search
+// radius of every cell with children set to 0 (k_rsmax raises it).
 __global__ __launch_bounds__(kThreads) void k_gather_radii(const double *r_in, const double *r_out,
                                                            const double *r_search, TreeDev t,
                                                            Status *st) {
@@ -854,33 +998,29 @@ __global__ __launch_bounds__(kThreads) void k_gather_radii(const double *r_in, c
         t.rr[k] = make_double2(a, b);
         t.rsk[k] = c;
     }
+    const int64_t n_nodes = *t.n_nodes_dev;
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_nodes;
+         c += (int64_t)gridDim.x * blockDim.x)
+        if (!(t.nd_info[c].z & kLeafFlag)) t.nd_lo[c].w = 0.0;
     if (__ballot(bad) && lane_id() == 0) atomicAdd(&st->invalid_radii, 1);
 }
 
-// Largest search radius per cell. Leaves take the maximum over their
-// particles and other cells start at 0; then every leaf raises its ancestors
-// with a 64-bit atomicMax on the bits of the value (the order of
-// non-negative doubles is that of their bits), climbing only while it raised
-// the cell above, since otherwise the value there came from another leaf
-// that climbs on. The result does not depend on the order of the atomics.
-__global__ __launch_bounds__(kThreads) void k_rsmax_leaves(TreeDev t) {
+// Largest search radius per cell. A leaf takes the maximum over its
+// particles and raises its ancestors (0 before) with a 64-bit atomicMax on
+// the bits of the value (the order of non-negative doubles is that of their
+// bits), climbing only while it raised the cell above, since otherwise the
+// value there came from another leaf that climbs on. The result does not
+// depend on the order of the atomics.
+__global__ __launch_bounds__(kThreads) void k_rsmax(TreeDev t) {
     const int64_t n_nodes = *t.n_nodes_dev;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_nodes;
          c += (int64_t)gridDim.x * blockDim.x) {
         const uint4 info = t.nd_info[c];
+        if (!(info.z & kLeafFlag)) continue;
         double r = 0.0;
-        if (info.z & kLeafFlag)
-            for (uint32_t k = info.x; k < info.x + info.y; k++) r = fmax(r, t.rsk[k]);
+        for (uint32_t k = info.x; k < info.x + info.y; k++) r = fmax(r, t.rsk[k]);
         t.nd_lo[c].w = r;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_rsmax_up(TreeDev t) {
-    const int64_t n_nodes = *t.n_nodes_dev;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_nodes;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        if (!(t.nd_info[c].z & kLeafFlag)) continue;
-        const unsigned long long v = (unsigned long long)__double_as_longlong(t.nd_lo[c].w);
+        const unsigned long long v = (unsigned long long)__double_as_longlong(r);
         for (uint32_t p = t.nd_parent[c]; p != kNone; p = t.nd_parent[p]) {
             const unsigned long long old =
                 atomicMax((unsigned long long *)&t.nd_lo[p].w, v);
@@ -939,22 +1079,23 @@ __global__ __launch_bounds__(kThreads) void k_mass_partial(const double *mass, i
     }
 }
 
-// Mean mass <m> = (sum m)/N, summed in a fixed order (deterministic).
-// Mean mass from the block partials: one wave, strided partial sums, then a
-// butterfly (a fixed order, so the result is reproducible).
-__global__ void k_mass_final(double *part, int nblk, int64_t n) {
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kWave) v += part[b];
-    v = wave_sum(v);
-    if (threadIdx.x == 0) part[nblk] = v / (double)n;
-}
-
+// Mean mass <m> = (sum m)/N from the block partials, by every block: one
+// wave, strided partial sums, then a butterfly (a fixed order, so the result
+// is reproducible).
 __global__ __launch_bounds__(kThreads) void k_radii(const double *mass, const double *vel,
-                                                    int64_t n, const double *mave_p,
+                                                    int64_t n, const double *part, int nblk,
                                                     double rin_ref, double rout_ref,
                                                     double search_factor, double cr_dt,
                                                     double *r_in, double *r_out, double *r_s) {
-    const double mave = *mave_p;
+    __shared__ double mean;
+    if (threadIdx.x < kWave) {
+        double v = 0.0;
+        for (int b = threadIdx.x; b < nblk; b += kWave) v += part[b];
+        v = wave_sum(v);
+        if (threadIdx.x == 0) mean = v / (double)n;
+    }
+    __syncthreads();
+    const double mave = mean;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         double ratio = mave > 0.0 ? mass[i] / mave : 1.0;
@@ -974,18 +1115,24 @@ __global__ __launch_bounds__(kThreads) void k_radii(const double *mass, const do
 }  // namespace
 
 // ------------------------------------------------------------ launchers
-int bbox_partial_blocks(int64_t n) { return (int)grid_for(n, kThreads, kBBoxBlocks); }
-
-void launch_bbox(const double *pos, const double *mass, int64_t n, double *part, RootBox *rb,
-                 hipStream_t s) {
-    int nb = bbox_partial_blocks(n);
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kThreads), 0, s, pos, mass, n, part, rb);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kThreads), 0, s, (const double *)part, nb, rb);
+int bbox_partial_blocks(int64_t n, int n_sys) {
+    // one block up to 8192 particles, else a block for every 1024 (of a mean
+    // system, four times that for the large ones of a batch)
+    const int64_t mean = n / n_sys;
+    const int64_t per = n_sys > 1 ? mean / 256 : (mean <= 8192 ? 1 : (mean + 1023) / 1024);
+    const int64_t most = n_sys > 1 ? 64 : kBBoxBlocks;
+    return n_sys * (int)(per < 1 ? 1 : (per > most ? most : per));
 }
 
-void launch_bbox_systems(const double *pos, const double *mass, int64_t n, const int64_t *off,
-                         int n_sys, RootBox *rb, hipStream_t s) {
-    hipLaunchKernelGGL(k_bbox_systems, dim3(n_sys), dim3(kThreads), 0, s, pos, mass, n, off, rb);
+void launch_bbox(const double *pos, const double *mass, int64_t n, const int64_t *off, int n_sys,
+                 double *part, RootBox *rb, hipStream_t s) {
+    const double cells = ldexp(1.0, off ? kBatchLevels : kMaxLevel);
+    const int nblk = bbox_partial_blocks(n, n_sys) / n_sys;
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nblk, n_sys), dim3(kThreads), 0, s, pos, mass, n, off,
+                       part, rb, cells);
+    if (nblk > 1)
+        hipLaunchKernelGGL(k_bbox_final, dim3(n_sys), dim3(kThreads), 0, s, (const double *)part,
+                           nblk, rb, cells);
 }
 
 void launch_keys_systems(const double *pos, int64_t n, const int64_t *off, int n_sys,
@@ -1008,33 +1155,64 @@ int64_t sort_ws_bytes(int64_t n) {
 
 void radix_sort(uint64_t **key, uint32_t **val, uint64_t **key_alt, uint32_t **val_alt, int64_t n,
                 int passes, void *ws, hipStream_t s, const int64_t *n_dev) {
+    if (n <= kOneThreads * 8) {  // one block; the result where the passes would end
+        uint64_t *ko = passes % 2 ? *key_alt : *key;
+        uint32_t *vo = passes % 2 ? *val_alt : *val;
+#define SORT_ONE(Per)                                                                          \
+    hipLaunchKernelGGL(k_sort_one<Per>, dim3(1), dim3(kOneThreads), 0, s,                      \
+                       (const uint64_t *)*key, (const uint32_t *)*val, ko, vo, n, passes, n_dev)
+        if (n <= kOneThreads)
+            SORT_ONE(1);
+        else if (n <= kOneThreads * 2)
+            SORT_ONE(2);
+        else if (n <= kOneThreads * 4)
+            SORT_ONE(4);
+        else
+            SORT_ONE(8);
+#undef SORT_ONE
+        if (passes % 2) {
+            std::swap(*key, *key_alt);
+            std::swap(*val, *val_alt);
+        }
+        return;
+    }
     int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    if (ntiles < 1) ntiles = 1;
     uint32_t *hist = (uint32_t *)ws;
     uint32_t *offs = hist + kRadix * ntiles;
     uint32_t *dtot = offs + kRadix * ntiles;
+    const dim3 g((unsigned)ntiles), b(kThreads);
     for (int pass = 0; pass < passes; pass++) {
         int shift = 8 * pass;
-        hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)ntiles), dim3(kThreads), 0, s,
-                           (const uint64_t *)*key, n, shift, hist, ntiles, n_dev);
-        hipLaunchKernelGGL(k_sort_rowscan, dim3(kRadix), dim3(kThreads), 0, s,
-                           (const uint32_t *)hist, ntiles, offs, dtot);
-        hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)ntiles), dim3(kThreads), 0, s,
-                           (const uint64_t *)*key, (const uint32_t *)*val, *key_alt, *val_alt, n,
-                           shift, (const uint32_t *)hist, (const uint32_t *)offs,
-                           (const uint32_t *)dtot, ntiles, n_dev);
-        uint64_t *tk = *key;
-        *key = *key_alt;
-        *key_alt = tk;
-        uint32_t *tv = *val;
-        *val = *val_alt;
-        *val_alt = tv;
+        if (ntiles <= kFewTiles) {
+            hipLaunchKernelGGL(k_sort_hist<true>, g, b, 0, s, (const uint64_t *)*key, n, shift,
+                               hist, ntiles, n_dev);
+            hipLaunchKernelGGL(k_sort_scatter<true>, g, b, 0, s, (const uint64_t *)*key,
+                               (const uint32_t *)*val, *key_alt, *val_alt, n, shift,
+                               (const uint32_t *)hist, (const uint32_t *)nullptr,
+                               (const uint32_t *)nullptr, ntiles, n_dev);
+        } else {
+            hipLaunchKernelGGL(k_sort_hist<false>, g, b, 0, s, (const uint64_t *)*key, n, shift,
+                               hist, ntiles, n_dev);
+            hipLaunchKernelGGL(k_sort_rowscan, dim3(kRadix), b, 0, s, (const uint32_t *)hist,
+                               ntiles, offs, dtot);
+            hipLaunchKernelGGL(k_sort_scatter<false>, g, b, 0, s, (const uint64_t *)*key,
+                               (const uint32_t *)*val, *key_alt, *val_alt, n, shift,
+                               (const uint32_t *)hist, (const uint32_t *)offs,
+                               (const uint32_t *)dtot, ntiles, n_dev);
+        }
+        std::swap(*key, *key_alt);
+        std::swap(*val, *val_alt);
     }
 }
 
 void launch_gather_particles(const double *pos, const double *mass, const uint32_t *idx,
                              int64_t n, double4 *ps, uint32_t *orig, uint32_t *rank,
                              hipStream_t s) {
+    if (n <= kGatherMax) {
+        hipLaunchKernelGGL(k_gather_all, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, s,
+                           pos, mass, idx, n, ps, orig, rank);
+        return;
+    }
     hipLaunchKernelGGL(k_rank, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, s, idx, n,
                        orig, rank);
     hipLaunchKernelGGL(k_scatter_particles, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0,
@@ -1048,40 +1226,41 @@ void launch_octree_count(const uint64_t *key, int64_t n, int leaf_size, int leve
 }
 
 void launch_build_head(const int64_t *base, int64_t n, const RootBox *rb,
-                       const uint32_t *deep_slots, Status *st, hipStream_t s) {
-    hipLaunchKernelGGL(k_build_head, dim3(1), dim3(kWave), 0, s, base, n, rb, deep_slots, st);
+                       const uint32_t *deep_slots, int64_t *host, hipStream_t s) {
+    hipLaunchKernelGGL(k_build_head, dim3(1), dim3(kWave), 0, s, base, n, rb, deep_slots, host);
 }
 
 void launch_octree_write(const uint64_t *key, int64_t n, int leaf_size, int levels,
                          const int64_t *base, PreOrder pre, uint64_t *lkey, uint32_t *lval,
                          int64_t node_cap, Status *st, hipStream_t s) {
-    hipLaunchKernelGGL(k_cell_count, dim3(1), dim3(64), 0, s, base, n, node_cap, st);
     hipLaunchKernelGGL(k_octree_emit, dim3(grid_for(n)), dim3(kThreads), 0, s, key, n, levels,
-                       base, pre, (const Status *)st);
+                       base, pre, node_cap, st);
     hipLaunchKernelGGL(k_octree_write, dim3(grid_for(node_cap)), dim3(kThreads), 0, s, key, n,
                        leaf_size, levels, base, pre, lkey, lval, (const Status *)st);
 }
 
-void launch_relayout(const uint32_t *perm, PreOrder pre, const RootBox *rb, const uint64_t *key,
-                     int levels, TreeDev t, uint32_t *level_off, hipStream_t s) {
-    hipLaunchKernelGGL(k_invert, dim3(grid_for(t.n_nodes)), dim3(kThreads), 0, s, perm,
-                       t.n_nodes_dev, pre.new_of_old);
+void launch_relayout(const uint32_t *perm, const uint64_t *lkey, PreOrder pre, const RootBox *rb,
+                     const uint64_t *key, int levels, TreeDev t, uint32_t *level_off, Status *st,
+                     uint32_t *leaf_slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_invert, dim3(grid_for(t.n_nodes)), dim3(kThreads), 0, s, perm, lkey,
+                       t.n_nodes_dev, pre.new_of_old, level_off);
     hipLaunchKernelGGL(k_relayout, dim3(grid_for(t.n_nodes)), dim3(kThreads), 0, s, perm, pre, rb,
-                       key, levels, t);
-    hipLaunchKernelGGL(k_level_offsets, dim3(1), dim3(32), 0, s, t, level_off);
+                       key, levels, t, st, leaf_slots);
 }
 
-void launch_moments(const TreeDev &t, int levels, hipStream_t s) {
+void launch_moments(const TreeDev &t, int levels, int n_sys, hipStream_t s) {
     hipLaunchKernelGGL(k_moments_leaves, dim3(grid_for(t.n_nodes, kThreads, 8192)), dim3(kThreads),
                        0, s, t);
-    for (int l = levels - 1; l >= 0; l--)
+    // one block takes every level of a small tree, else the levels at the top
+    // that cannot hold more than 512 cells
+    int top = levels - 1;
+    if (t.n_nodes > kSmallTree)
+        for (top = -1; top + 1 < levels && ((int64_t)n_sys << (3 * (top + 1))) <= 512;) top++;
+    for (int l = levels - 1; l > top; l--)
         hipLaunchKernelGGL(k_moments_level, dim3(grid_for(t.n_nodes, kThreads, 1024)),
                            dim3(kThreads), 0, s, t, l);
-}
-
-void launch_tree_summary(const TreeDev &t, Status *st, hipStream_t s) {
-    hipLaunchKernelGGL(k_tree_summary, dim3(grid_for(t.n_nodes, kThreads, 256)), dim3(kThreads), 0,
-                       s, t, st);
+    if (top >= 0)
+        hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(kTopThreads), 0, s, t, top);
 }
 
 void launch_gather_radii(const double *r_in, const double *r_out, const double *r_search,
@@ -1091,9 +1270,7 @@ void launch_gather_radii(const double *r_in, const double *r_out, const double *
 }
 
 void launch_rsmax(const TreeDev &t, hipStream_t s) {
-    hipLaunchKernelGGL(k_rsmax_leaves, dim3(grid_for(t.n_nodes, kThreads, 8192)), dim3(kThreads), 0,
-                       s, t);
-    hipLaunchKernelGGL(k_rsmax_up, dim3(grid_for(t.n_nodes, kThreads, 8192)), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(k_rsmax, dim3(grid_for(t.n_nodes, kThreads, 8192)), dim3(kThreads), 0, s,
                        t);
 }
 
@@ -1114,9 +1291,8 @@ void launch_changeover_radii(const double *mass, const double *vel, int64_t n, d
                              double *r_out, double *r_search, double *ws, hipStream_t s) {
     int nb = (int)grid_for(n, kThreads, 1024);
     hipLaunchKernelGGL(k_mass_partial, dim3(nb), dim3(kThreads), 0, s, mass, n, ws);
-    hipLaunchKernelGGL(k_mass_final, dim3(1), dim3(64), 0, s, ws, nb, n);
-    hipLaunchKernelGGL(k_radii, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, s, mass, vel,
-                       n, (const double *)(ws + nb), rin_ref, rout_ref, search_factor, cr_dt, r_in,
+    hipLaunchKernelGGL(k_radii, dim3(grid_for(n, kThreads, 2048)), dim3(kThreads), 0, s, mass, vel,
+                       n, (const double *)ws, nb, rin_ref, rout_ref, search_factor, cr_dt, r_in,
                        r_out, r_search);
 }
 

@@ -1531,3 +1531,80 @@ def test_filter_and_clusters_row_shapes(pt, orc, n):
         pt.petar_destroy(ctx)
     for a, b in zip(*results):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2049, 8192, 8193, 16385, 131072, 131073, 262144,
+                               262145])
+def test_build_at_size_edges(pt, orc, n):
+    """Star numbers around the lines between the build's kernels (one block,
+    few tiles, many tiles), with stars at equal positions among them: tree
+    shape and groups of the oracle's tree, forces and neighbour rows of a
+    sample, and the captured step equal to the eager calls bit for bit, also
+    when the positions change between its replays."""
+    leaf, group = 2, 32
+    c, rin, rout, rs = cluster_with_radii(orc, n, 80 + n, rin_ref=0.6 / n ** 0.5,
+                                          rout_ref=6.0 / n ** 0.5)
+    c.pos[:, 1::97] = c.pos[:, 0:-1:97][:, :c.pos[:, 1::97].shape[1]]
+    s = workloads.sample_indices(n, 256, 0)
+    ctx, graph = pt.petar_create(0), pt.petar_create(0)
+    dpos, dmass, drin, drout, drs = T(c.pos), T(c.mass), T(rin), T(rout), T(rs)
+    acc = torch.empty((3, n), dtype=torch.float64, device="cuda:0")
+    pot = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    nbo = torch.empty(n + 1, dtype=torch.int64, device="cuda:0")
+    nbi = torch.empty(128 * n, dtype=torch.int32, device="cuda:0")
+    pt.petar_set_params(ctx, precision=pt.PETAR_FP64, record_counts=1)
+    pt.petar_set_params(graph, precision=pt.PETAR_FP64)
+    for it in range(3):
+        if it == 2:
+            c.pos[:] = c.pos[:, ::-1].copy()
+            dpos.copy_(T(c.pos))
+        pt.petar_tree_build(ctx, dpos, dmass, 0.5, leaf)
+        a, p, (o, i) = pt.petar_force_long(ctx, group, drin, drout, drs, nb_capacity=128 * n)
+        tot = pt.petar_step_graph(graph, dpos, dmass, 0.5, leaf, group, drin, drout, drs, acc,
+                                  pot, nb=(nbo, nbi))
+        assert torch.equal(acc, a) and torch.equal(pot, p)
+        assert torch.equal(nbo, o) and torch.equal(nbi[:tot], i)
+        if it == 1:
+            continue
+        st = pt.petar_get_stats(ctx)
+        ref = orc.tree_info(c.pos, c.mass, leaf, group)
+        assert (st["n_nodes"], st["n_leaves"], st["n_groups"], st["max_level"]) == \
+            (ref["n_cells"], ref["n_leaves"], ref["n_groups"], ref["max_level"])
+        a_ref, p_ref, cnt_ref = orc.tree_force(c.pos, c.mass, rin, rout, rs, 0.5, leaf, group,
+                                               idx=s)
+        same = np.all(pt.petar_copy_counts(ctx).cpu().numpy()[:, s] == cnt_ref, axis=0)
+        assert same.mean() > 0.995
+        assert rel_err(a.cpu().numpy()[:, s], a_ref)[same].max() < 1e-11
+        np.testing.assert_allclose(p.cpu().numpy()[s][same], p_ref[same], rtol=1e-11)
+        o_ref, i_ref = orc.neighbours(c.pos, rs, idx=s)
+        o, i = o.cpu().numpy(), i.cpu().numpy()
+        for k, j in enumerate(s):
+            assert np.array_equal(i[o[j]:o[j + 1]], i_ref[o_ref[k]:o_ref[k + 1]])
+    pt.petar_destroy(ctx)
+    pt.petar_destroy(graph)
+
+
+def test_step_graph_when_handover_overflows(pt, orc):
+    """A captured step whose near leaves overflow the hand-over buffers gives
+    the lists of the walk-based passes in the call that finds it, and the
+    same lists in the calls that follow."""
+    c = workloads.make_cluster(4000, 23, imf=True, binary_fraction=0.5)
+    n = c.mass.size
+    rin, rout, few = orc.radii(c.mass, 0.005, 0.02, 1.2)
+    rs = orc.radii(c.mass, 0.05, 0.2, 3.0)[2]
+    o_ref, i_ref = orc.neighbours(c.pos, rs)
+    acc = torch.empty((3, n), dtype=torch.float64, device="cuda:0")
+    pot = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    nbo = torch.empty(n + 1, dtype=torch.int64, device="cuda:0")
+    nbi = torch.empty(int(o_ref[-1]), dtype=torch.int32, device="cuda:0")
+    dpos, dmass, drin, drout, drs = T(c.pos), T(c.mass), T(rin), T(rout), T(few)
+    ctx = pt.petar_create(0)
+    for it in range(5):
+        if it == 2:  # same buffers: the replay meets the larger radii
+            drs.copy_(T(rs))
+        tot = pt.petar_step_graph(ctx, dpos, dmass, 0.5, 8, 64, drin, drout, drs, acc, pot,
+                                  nb=(nbo, nbi))
+        if it >= 2:
+            assert tot == o_ref[-1] and np.array_equal(nbo.cpu().numpy(), o_ref)
+            assert np.array_equal(nbi[:tot].cpu().numpy(), i_ref)
+    pt.petar_destroy(ctx)
