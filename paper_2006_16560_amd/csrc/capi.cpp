@@ -1031,8 +1031,8 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     launch_gather_radii(a.r_in, a.r_out, a.r_search, t, st, s);
     launch_rsmax(t, s);
     launch_group_flags(pre, t, a.group_size, ptr<uint32_t>(ctx->gflag), s);
-    scan_u32_to_u32(ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos), n_nodes,
-                    ptr<int64_t>(ctx->scan_ws), s);
+    scan_classes(ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos), n_nodes, &st->n_big,
+                 ptr<int64_t>(ctx->scan_ws), s);
     launch_group_compact(pre, t, ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos),
                          ptr<uint32_t>(ctx->groups), st, s);
     const uint32_t *tpos = nullptr, *tidx = nullptr;

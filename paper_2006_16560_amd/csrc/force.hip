@@ -646,6 +646,21 @@ __device__ __forceinline__ void kick_add(double *v, double a, double dt) {
     *v = *v + a * dt;
 }
 
+// Queue q's groups: its eighth of the n_big large ones, which are listed
+// first, then its eighth of the others.
+__device__ __forceinline__ uint32_t eighths(uint32_t n, int q) {
+    return (n >> 3) * (uint32_t)q + ((n & 7u) * (uint32_t)q >> 3);  // n q / 8
+}
+__device__ __forceinline__ uint32_t queue_size(uint32_t groups, uint32_t big, int q) {
+    const uint32_t rest = groups - big;
+    return eighths(big, q + 1) - eighths(big, q) + eighths(rest, q + 1) - eighths(rest, q);
+}
+__device__ __forceinline__ uint32_t queue_group(uint32_t groups, uint32_t big, int q, uint32_t v) {
+    const uint32_t rest = groups - big;
+    const uint32_t first = eighths(big, q), many = eighths(big, q + 1) - first;
+    return v < many ? first + v : big + eighths(rest, q) + (v - many);
+}
+
 // Work queues, one per XCD: contiguous ranges of the groups (Morton order);
 // a worker whose queue is empty goes on to the next one. A queue that may be
 // empty is looked at before it is claimed from (a stale head costs one claim
@@ -656,36 +671,36 @@ __device__ __forceinline__ void kick_add(double *v, double a, double dt) {
 // without a claim; with few groups there is no claim at all.
 struct GroupQueue {
     uint32_t *heads;
-    int64_t n_groups;
+    uint32_t n_groups, n_big;
     uint32_t rank;  // this worker's in its queue
     int q, moves;
     bool first, sure;
 
-    __device__ __forceinline__ GroupQueue(uint32_t *h, int64_t n)
-        : heads(h), n_groups(n), rank(blockIdx.x >> 3), q((int)(blockIdx.x & 7u)), moves(0),
+    __device__ __forceinline__ GroupQueue(uint32_t *h, const Status *s)
+        : heads(h), n_groups((uint32_t)s->n_groups), n_big((uint32_t)s->n_big), rank(blockIdx.x >> 3), q((int)(blockIdx.x & 7u)), moves(0),
           first(true), sure(false) {}
 
     // Next group of this wave, -1 when all are taken.
     __device__ __forceinline__ int64_t next() {
         while (moves < 8) {
-            const int64_t lo = n_groups * q / 8, size = n_groups * (q + 1) / 8 - lo;
+            const uint32_t size = queue_size(n_groups, n_big, q);
             const uint32_t nstat = (gridDim.x + 7u - (uint32_t)q) >> 3;
-            int64_t v = size;
+            uint32_t v = size;
             if (first) {
                 v = rank;
-            } else if (size > (int64_t)nstat) {
+            } else if (size > nstat) {
                 uint32_t h = 0;
                 if (lane_id() == 0) {
                     uint32_t *head = heads + q * kQueueStride;
                     if (!sure)
                         h = __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (sure || (int64_t)nstat + h < size) h = atomicAdd(head, 1u);
+                    if (sure || nstat + h < size) h = atomicAdd(head, 1u);
                 }
-                v = (int64_t)nstat + (uint32_t)uniform((int)h);
+                v = nstat + (uint32_t)uniform((int)h);
             }
             first = false;
-            sure = v + 2 * (int64_t)nstat < size;  // not yet near the end
-            if (v < size) return lo + v;
+            sure = v + 2 * nstat < size;  // not yet near the end
+            if (v < size) return queue_group(n_groups, n_big, q, v);
             moves++;
             q = (q + 1) & 7;
         }
@@ -704,7 +719,7 @@ __global__ __launch_bounds__(kThreads, sizeof(R) == 4 && IPL == 2 ? 4 : 1) void 
     const int lane = lane_id();
     const int64_t gwave = (int64_t)blockIdx.x * kWavesPerBlock + w;
     if (f.st_in->invalid_radii || f.st_in->cell_overflow) return;
-    const int64_t n_groups = f.st_in->n_groups;
+    const uint32_t n_groups = (uint32_t)f.st_in->n_groups, n_big = (uint32_t)f.st_in->n_big;
     const int64_t n = f.t.n;
     WaveStack stk;
     stk.lds = L.stack;
@@ -719,17 +734,17 @@ __global__ __launch_bounds__(kThreads, sizeof(R) == 4 && IPL == 2 ? 4 : 1) void 
     int moves = 0;
     const int CH = kWave * IPL;
     while (true) {
-        const int64_t qlo = n_groups * q / 8, qhi = n_groups * (q + 1) / 8;
+        const uint32_t size = queue_size(n_groups, n_big, q);
         uint32_t v = 0;
         if (lane == 0) {
             uint32_t *head = f.queue + q * kQueueStride;
             if (moves > 0)
                 v = __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (qlo + (int64_t)v < qhi) v = atomicAdd(head, 1u);
+            if (v < size) v = atomicAdd(head, 1u);
         }
         v = (uint32_t)uniform((int)v);
-        const int64_t g = qlo + (int64_t)v;
-        if (g >= qhi) {
+        const int64_t g = queue_group(n_groups, n_big, q, v);
+        if (v >= size) {
             if (++moves >= 8) break;
             q = (q + 1) & 7;
             continue;
@@ -1271,14 +1286,14 @@ __global__ __launch_bounds__(T *kWave, MW) void k_force_team(ForceLaunch f) {
     if (f.st_in->invalid_radii || f.st_in->cell_overflow) return;
     const int w = uniform((int)(threadIdx.x / kWave));
     const int lane = lane_id();
-    const int64_t n = f.t.n, n_groups = f.st_in->n_groups;
+    const int64_t n = f.t.n;
     // the walker's wave differs between the blocks of a CU (the grid's
     // quarters), so that the walks spread over its SIMDs
     const int walker = (int)((uint64_t)blockIdx.x * 4 / gridDim.x) % T;
     const uint32_t CH = kWave * IPL;
     unsigned long long cnt_pc = 0, cnt_far = 0, cnt_near = 0;
     for (int i = threadIdx.x; i < IPL * 4 * kWave; i += T * kWave) (&L.acc[0][0][0])[i] = 0.0;
-    GroupQueue queue(f.queue, n_groups);
+    GroupQueue queue(f.queue, f.st_in);
     int64_t g = -1;
     uint32_t gnode = 0, gstart = 0, gn = 0, t0 = 0, tn = 0;
     auto group = [&](int64_t which) {

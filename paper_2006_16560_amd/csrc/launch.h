@@ -18,6 +18,10 @@ void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, h
 // The same, and the counts are 0 afterwards.
 void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s);
 void scan_u32_to_u32(const uint32_t *in, uint32_t *out, int64_t n, int64_t *ws, hipStream_t s);
+// Flags 0, 1 or 2: out[i] = position of element i among those of its flag,
+// out[n] = number of ones and twos (below 2^32), *second (device) = of twos.
+void scan_classes(const uint32_t *flag, uint32_t *out, int64_t n, int64_t *second, int64_t *ws,
+                  hipStream_t s);
 // Up to kFillPieces small buffers of 32-bit words set to 0 in one launch.
 constexpr int kFillPieces = 4;
 struct FillWords {
@@ -112,7 +116,9 @@ void launch_moments(const TreeDev &t, int levels, int n_sys, hipStream_t s);
 void launch_gather_radii(const double *r_in, const double *r_out, const double *r_search,
                          TreeDev t, Status *st, hipStream_t s);
 void launch_rsmax(const TreeDev &t, hipStream_t s);
-// flag[] is written for every slot up to t.n_nodes (the capacity), 0 past the cells.
+// flag[] is written for every slot up to t.n_nodes (the capacity): 0 for a cell
+// that is no group (and past the cells), 1 or, with more than half of
+// group_size particles, 2. The groups are listed with the twos first.
 void launch_group_flags(const PreOrder &pre, const TreeDev &t, int group_size, uint32_t *flag,
                         hipStream_t s);
 void launch_group_compact(const PreOrder &pre, const TreeDev &t, const uint32_t *flag,

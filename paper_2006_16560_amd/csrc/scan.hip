@@ -36,14 +36,36 @@ __device__ int64_t block_excl_scan(int64_t v, int64_t *total) {
     return off + incl - v;
 }
 
-template <typename In>
+// What a scan makes of its counts: the counts themselves, or (Classes) flags
+// 0, 1 and 2 of which the ones and the twos are counted side by side, in the
+// halves of a word: every flagged element gets its position in its class,
+// out[n] is the number of both and *second that of the twos.
+struct Plain {
+    __device__ static int64_t value(uint32_t f) { return (int64_t)f; }
+    __device__ static int64_t place(int64_t, int64_t before) { return before; }
+    __device__ static int64_t total(int64_t t, int64_t *) { return t; }
+};
+struct Classes {
+    __device__ static int64_t value(uint32_t f) {
+        return f == 2u ? (int64_t)1 << 32 : (int64_t)f;
+    }
+    __device__ static int64_t place(int64_t v, int64_t before) {
+        return v >> 32 ? before >> 32 : before & 0xffffffffll;
+    }
+    __device__ static int64_t total(int64_t t, int64_t *second) {
+        *second = t >> 32;
+        return (t >> 32) + (t & 0xffffffffll);
+    }
+};
+
+template <typename In, typename Map>
 __global__ __launch_bounds__(kScanThreads) void k_block_totals(const In *in, int64_t n,
                                                                int64_t *bsum) {
     int64_t base = (int64_t)blockIdx.x * kScanTile;
     int64_t v = 0;
     for (int k = 0; k < kScanItems; k++) {
         int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
-        if (i < n) v += (int64_t)in[i];
+        if (i < n) v += Map::value(in[i]);
     }
     int64_t tot;
     block_excl_scan(v, &tot);
@@ -67,9 +89,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_totals(int64_t *bsum, int
 // Block-local scan plus the sum of the earlier blocks: bsum holds the
 // totals, added up here (kSelf), or already their prefix sums. kClear: the
 // counts are set to 0 once read.
-template <typename In, typename Out, bool kSelf, bool kClear>
+template <typename In, typename Out, typename Map, bool kSelf, bool kClear>
 __global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, int64_t n,
-                                                             const int64_t *bsum, int64_t nb) {
+                                                             const int64_t *bsum, int64_t nb,
+                                                             int64_t *second) {
     int64_t before = 0;
     if constexpr (kSelf) {
         int64_t part = 0;
@@ -84,7 +107,7 @@ __global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, i
 #pragma unroll
     for (int k = 0; k < kScanItems; k++) {
         int64_t i = base + k;
-        vals[k] = i < n ? (int64_t)in[i] : 0;
+        vals[k] = i < n ? Map::value(in[i]) : 0;
         s += vals[k];
     }
     if constexpr (kClear) {
@@ -97,15 +120,16 @@ __global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, i
 #pragma unroll
     for (int k = 0; k < kScanItems; k++) {
         int64_t i = base + k;
-        if (i < n) out[i] = (Out)off;
+        if (i < n) out[i] = (Out)Map::place(vals[k], off);
         off += vals[k];
     }
-    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = (Out)(before + tot);
+    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[n] = (Out)Map::total(before + tot, second);
 }
 
 // The whole scan by one block, kOneThreads * Items counts at a time.
-template <typename In, typename Out, bool kClear>
-__global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int64_t n) {
+template <typename In, typename Out, typename Map, bool kClear>
+__global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int64_t n,
+                                                          int64_t *second) {
     constexpr int Items = 4;
     int64_t carry = 0;
     for (int64_t c = 0; c < n; c += (int64_t)kOneThreads * Items) {
@@ -113,7 +137,7 @@ __global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int6
         int64_t vals[Items], s = 0;
 #pragma unroll
         for (int k = 0; k < Items; k++) {
-            vals[k] = base + k < n ? (int64_t)in[base + k] : 0;
+            vals[k] = base + k < n ? Map::value(in[base + k]) : 0;
             s += vals[k];
         }
         int64_t tot;
@@ -121,14 +145,14 @@ __global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int6
 #pragma unroll
         for (int k = 0; k < Items; k++) {
             if (base + k < n) {
-                out[base + k] = (Out)off;
+                out[base + k] = (Out)Map::place(vals[k], off);
                 if constexpr (kClear) in[base + k] = 0;
             }
             off += vals[k];
         }
         carry += tot;
     }
-    if (threadIdx.x == 0) out[n] = (Out)carry;
+    if (threadIdx.x == 0) out[n] = (Out)Map::total(carry, second);
 }
 
 template <typename T>
@@ -155,25 +179,26 @@ __global__ void k_words_out(const int64_t *words, int n, int64_t *host) {
     if ((int)threadIdx.x < n) host[threadIdx.x] = words[threadIdx.x];
 }
 
-template <typename In, typename Out, bool kClear>
-void scan_impl(In *in, Out *out, int64_t n, int64_t *ws, hipStream_t s) {
+template <typename In, typename Out, typename Map, bool kClear>
+void scan_impl(In *in, Out *out, int64_t n, int64_t *ws, hipStream_t s,
+               int64_t *second = nullptr) {
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (nb < 1) nb = 1;
     if (nb <= kOneBlockTiles) {
-        hipLaunchKernelGGL((k_scan_one<In, Out, kClear>), dim3(1), dim3(kOneThreads), 0, s, in,
-                           out, n);
+        hipLaunchKernelGGL((k_scan_one<In, Out, Map, kClear>), dim3(1), dim3(kOneThreads), 0, s,
+                           in, out, n, second);
         return;
     }
     const dim3 g((unsigned)nb), b(kScanThreads);
-    hipLaunchKernelGGL(k_block_totals<In>, g, b, 0, s, (const In *)in, n, ws);
+    hipLaunchKernelGGL((k_block_totals<In, Map>), g, b, 0, s, (const In *)in, n, ws);
     if (nb <= kSelfTotals) {
-        hipLaunchKernelGGL((k_block_scan<In, Out, true, kClear>), g, b, 0, s, in, out, n,
-                           (const int64_t *)ws, nb);
+        hipLaunchKernelGGL((k_block_scan<In, Out, Map, true, kClear>), g, b, 0, s, in, out, n,
+                           (const int64_t *)ws, nb, second);
         return;
     }
     hipLaunchKernelGGL(k_scan_totals, dim3(1), b, 0, s, ws, nb);
-    hipLaunchKernelGGL((k_block_scan<In, Out, false, kClear>), g, b, 0, s, in, out, n,
-                       (const int64_t *)ws, nb);
+    hipLaunchKernelGGL((k_block_scan<In, Out, Map, false, kClear>), g, b, 0, s, in, out, n,
+                       (const int64_t *)ws, nb, second);
 }
 
 template <typename T>
@@ -189,13 +214,18 @@ void fill_impl(T *p, T v, int64_t n, hipStream_t s) {
 int64_t scan_ws_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
 
 void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl<uint32_t, int64_t, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+    scan_impl<uint32_t, int64_t, Plain, false>(const_cast<uint32_t *>(in), out, n, ws, s);
 }
 void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl<uint32_t, int64_t, true>(in, out, n, ws, s);
+    scan_impl<uint32_t, int64_t, Plain, true>(in, out, n, ws, s);
 }
 void scan_u32_to_u32(const uint32_t *in, uint32_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl<uint32_t, uint32_t, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+    scan_impl<uint32_t, uint32_t, Plain, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+}
+void scan_classes(const uint32_t *flag, uint32_t *out, int64_t n, int64_t *second, int64_t *ws,
+                  hipStream_t s) {
+    scan_impl<uint32_t, uint32_t, Classes, false>(const_cast<uint32_t *>(flag), out, n, ws, s,
+                                                  second);
 }
 void fill_words(std::initializer_list<FillWords> pieces, hipStream_t s) {
     FillList l{};

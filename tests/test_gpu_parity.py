@@ -1608,3 +1608,27 @@ def test_step_graph_when_handover_overflows(pt, orc):
             assert tot == o_ref[-1] and np.array_equal(nbo.cpu().numpy(), o_ref)
             assert np.array_equal(nbi[:tot].cpu().numpy(), i_ref)
     pt.petar_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,leaf,group", [(1, 1, 1), (2, 2, 1), (5, 1, 1), (3000, 2, 3),
+                                          (3000, 8, 4096), (3000, 8, 8192), (20000, 1, 64)])
+def test_large_groups_listed_first(pt, ctx, orc, n, leaf, group):
+    """Groups of which all, none or some count as large (more than half of
+    group_size): their number, and every particle's interactions and force,
+    are those of the oracle's tree."""
+    c, rin, rout, rs = cluster_with_radii(orc, n, 90 + n, rin_ref=0.01, rout_ref=0.1)
+    pt.petar_set_params(ctx, precision=pt.PETAR_FP64, i_per_lane=2, record_counts=1)
+    pt.petar_tree_build(ctx, T(c.pos), T(c.mass), 0.5, leaf)
+    acc, pot = pt.petar_force_long(ctx, group, T(rin), T(rout), T(rs))
+    cnt = pt.petar_copy_counts(ctx).cpu().numpy()
+    pt.petar_set_params(ctx, precision=pt.PETAR_MIXED, i_per_lane=1, record_counts=0)
+    assert pt.petar_get_stats(ctx)["n_groups"] == \
+        orc.tree_info(c.pos, c.mass, leaf, group)["n_groups"]
+    a_ref, p_ref, cnt_ref = orc.tree_force(c.pos, c.mass, rin, rout, rs, 0.5, leaf, group)
+    same = np.all(cnt == cnt_ref, axis=0)
+    assert same.mean() > 0.995
+    if n > 1:
+        assert rel_err(acc.cpu().numpy(), a_ref)[same].max() < 1e-12
+        np.testing.assert_allclose(pot.cpu().numpy()[same], p_ref[same], rtol=1e-12)
+    else:
+        assert not acc.any() and not pot.any()
