@@ -394,10 +394,11 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
     }
 }
 
-// The whole sort by one block, every pass in LDS: Per keys a thread in
-// registers, ranked wave by wave as in k_sort_scatter. A pass in which all
-// keys have one digit moves nothing. Four thousand keys, 8 passes: 32 us
-// instead of 24 launches (170 us with their gaps in a captured graph).
+// Each block sorts its kOneThreads * Per keys, every pass in LDS: Per keys a
+// thread in registers, ranked wave by wave as in k_sort_scatter. A pass in
+// which all keys have one digit moves nothing. Four thousand keys, 8 passes,
+// one block: 32 us instead of 24 launches (170 us with their gaps in a
+// captured graph).
 constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / kWave;
 
@@ -413,6 +414,13 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint64_t *key_in
     __shared__ uint32_t wsum[kRadix / kWave];
     __shared__ int one_digit[2];  // by the parity of the pass
     if (n_dev) n = *n_dev;
+    const int64_t first_key = (int64_t)blockIdx.x * kOneThreads * Per;
+    key_in += first_key;
+    val_in += first_key;
+    key_out += first_key;
+    val_out += first_key;
+    n = n - first_key < kOneThreads * Per ? n - first_key : kOneThreads * Per;
+    if (n <= 0) return;
     const int t = threadIdx.x, w = t / kWave;
     const int pos0 = w * kWave * Per + lane_id();  // + r kWave
     uint64_t kk[Per];
@@ -477,6 +485,106 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint64_t *key_in
             key_out[k] = kk[r];
             val_out[k] = vv[r];
         }
+    }
+}
+
+// Merges tiles of kMergeTile sorted keys: a key's place is its place in its
+// tile plus the number of keys before it in each other tile (equal keys of an
+// earlier tile are before it, those of a later one behind: a stable sort). A
+// block takes kMergeKeys keys of a tile. It first brackets them in every
+// tile by searches for its first and last key, then each key is searched for
+// in the brackets, a few hundred keys that lie in few cache lines.
+// kMergeSplit waves share a key's tiles and search kMergeFlight of them in
+// step, so that the wait is for log2 of a bracket's loads, not for the tiles'
+// number of them.
+//
+// Tiles of 2048 keys up to 64k keys (sort and merge 21 + 18 us at 64k, where
+// eight passes of two launches took 115), then of 4096 (at 100k the merge takes
+// 30 us instead of 47; the passes took 130). The merge grows with
+// the square of the number of keys, which ends its range at kMergeMax.
+constexpr int kMergeSplit = 4;
+constexpr int kMergeKeys = kOneThreads / kMergeSplit;
+constexpr int kMergeFlight = 8;
+constexpr int kMergeTiles = 32;
+constexpr int64_t kMergeMax = (int64_t)kMergeTiles * 4 * kOneThreads;
+
+template <int Per>
+__global__ __launch_bounds__(kOneThreads) void k_sort_merge(const uint64_t *key_in,
+                                                            const uint32_t *val_in,
+                                                            uint64_t *key_out, uint32_t *val_out,
+                                                            int n, const int64_t *n_dev) {
+    constexpr int kMergeTile = Per * kOneThreads;
+    __shared__ int bracket[2][kMergeTiles];
+    __shared__ uint32_t part_sum[kMergeSplit][kMergeKeys];
+    if (n_dev) n = (int)*n_dev;
+    const int first = (int)blockIdx.x * kMergeKeys;
+    if (first >= n) return;
+    const int last = first + kMergeKeys < n ? first + kMergeKeys - 1 : n - 1;
+    const int ntiles = (n + kMergeTile - 1) / kMergeTile;
+    const int mine = first / kMergeTile;
+    const int t = threadIdx.x;
+    if (t < 2 * kMergeTiles && t % kMergeTiles < ntiles) {
+        // keys of tile b before the block's first key, and before its last
+        const int b = t % kMergeTiles, end = t / kMergeTiles;
+        const uint64_t x = key_in[end ? last : first];
+        const int base = b * kMergeTile;
+        int lo = 0, hi = n - base < kMergeTile ? n - base : kMergeTile;
+        while (lo < hi) {  // narrowed four-fold a round
+            const int len = hi - lo, m1 = lo + len / 4, m2 = lo + len / 2, m3 = lo + len * 3 / 4;
+            const uint64_t y1 = key_in[base + m1], y2 = key_in[base + m2], y3 = key_in[base + m3];
+            const bool eq = b < mine;
+            const bool l1 = y1 < x || (y1 == x && eq), l2 = y2 < x || (y2 == x && eq),
+                       l3 = y3 < x || (y3 == x && eq);
+            hi = l3 ? hi : l2 ? m3 : l1 ? m2 : m1;
+            lo = l3 ? m3 + 1 : l2 ? m2 + 1 : l1 ? m1 + 1 : lo;
+        }
+        bracket[end][b] = lo;
+    }
+    __syncthreads();
+    const int part = t / kMergeKeys, i = t % kMergeKeys;
+    const int k = first + i;
+    const uint64_t x = key_in[k <= last ? k : last];
+    uint32_t before = 0;
+    for (int t0 = part; t0 < ntiles; t0 += kMergeSplit * kMergeFlight) {
+        int lo[kMergeFlight], len[kMergeFlight], most = 0;
+#pragma unroll
+        for (int u = 0; u < kMergeFlight; u++) {
+            const int b = t0 + u * kMergeSplit;
+            const bool other = b < ntiles && b != mine;
+            lo[u] = other ? bracket[0][b] : 0;
+            len[u] = other ? bracket[1][b] - lo[u] : 0;
+            most = len[u] > most ? len[u] : most;
+        }
+        most = uniform(most);
+        while (most > 0) {
+            uint64_t y[kMergeFlight];
+#pragma unroll
+            for (int u = 0; u < kMergeFlight; u++)
+                y[u] = len[u] > 0 ? key_in[(t0 + u * kMergeSplit) * kMergeTile + lo[u] + len[u] / 2]
+                                  : 0ull;
+#pragma unroll
+            for (int u = 0; u < kMergeFlight; u++) {
+                const int half = len[u] / 2;
+                const bool less = y[u] < x || (y[u] == x && t0 + u * kMergeSplit < mine);
+                if (less && len[u] > 0) {
+                    lo[u] += half + 1;
+                    len[u] -= half + 1;
+                } else {
+                    len[u] = half;
+                }
+            }
+            most /= 2;  // no bracket is longer
+        }
+#pragma unroll
+        for (int u = 0; u < kMergeFlight; u++) before += (uint32_t)lo[u];
+    }
+    part_sum[part][i] = before;
+    __syncthreads();
+    if (part == 0 && k <= last) {
+        uint32_t p = (uint32_t)(k - mine * kMergeTile);
+        for (int q = 0; q < kMergeSplit; q++) p += part_sum[q][i];
+        key_out[p] = x;
+        val_out[p] = val_in[k];
     }
 }
 
@@ -1177,6 +1285,33 @@ void radix_sort(uint64_t **key, uint32_t **val, uint64_t **key_alt, uint32_t **v
         else
             SORT_ONE(8);
 #undef SORT_ONE
+        if (passes % 2) {
+            std::swap(*key, *key_alt);
+            std::swap(*val, *val_alt);
+        }
+        return;
+    }
+    // Up to kMergeMax keys, and if there is more than one pass (two launches
+    // each otherwise): sorted tiles, then merged.
+    if (n <= kMergeMax && passes > 1) {
+        uint64_t *kt = passes % 2 ? *key : *key_alt;
+        uint32_t *vt = passes % 2 ? *val : *val_alt;
+        uint64_t *ko = passes % 2 ? *key_alt : *key;
+        uint32_t *vo = passes % 2 ? *val_alt : *val;
+#define SORT_TILES(Per)                                                                        \
+    hipLaunchKernelGGL(k_sort_one<Per>,                                                        \
+                       dim3((unsigned)((n + Per * kOneThreads - 1) / (Per * kOneThreads))),    \
+                       dim3(kOneThreads), 0, s, (const uint64_t *)*key,                        \
+                       (const uint32_t *)*val, kt, vt, n, passes, n_dev);                      \
+    hipLaunchKernelGGL(k_sort_merge<Per>, dim3((unsigned)((n + kMergeKeys - 1) / kMergeKeys)), \
+                       dim3(kOneThreads), 0, s, (const uint64_t *)kt, (const uint32_t *)vt,    \
+                       ko, vo, (int)n, n_dev)
+        if (n <= kMergeTiles * 2 * kOneThreads) {
+            SORT_TILES(2);
+        } else {
+            SORT_TILES(4);
+        }
+#undef SORT_TILES
         if (passes % 2) {
             std::swap(*key, *key_alt);
             std::swap(*val, *val_alt);

@@ -1632,3 +1632,19 @@ def test_large_groups_listed_first(pt, ctx, orc, n, leaf, group):
         np.testing.assert_allclose(pot.cpu().numpy()[same], p_ref[same], rtol=1e-12)
     else:
         assert not acc.any() and not pot.any()
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 10240, 65536, 65537, 131071, 131072, 131073])
+@pytest.mark.parametrize("hubs", [1, 300, "third"])
+def test_members_sorted_at_size_edges(pt, ctx, orc, n, hubs):
+    """The sort of the cluster members (stable, equal keys in runs from a few
+    to all) at the sizes where its tiles change: one block, merged tiles of
+    two sizes, passes over all."""
+    m = n // 3 if hubs == "third" else hubs
+    offs = np.concatenate([np.zeros(m, dtype=np.int64), np.arange(n - m + 1, dtype=np.int64)])
+    idx = (np.random.default_rng(n).permutation(np.arange(m, n)) % m).astype(np.int32)
+    l_ref, cl_ref, m_ref = orc.clusters(n, offs, idx)
+    label, cl, members = pt.petar_clusters(ctx, T(offs), T(idx))
+    assert np.array_equal(label.cpu().numpy(), l_ref)
+    assert np.array_equal(cl.cpu().numpy(), cl_ref)
+    assert np.array_equal(members.cpu().numpy(), m_ref)
