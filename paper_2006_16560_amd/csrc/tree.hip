@@ -396,9 +396,8 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint64_t *key_i
 
 // Each block sorts its kOneThreads * Per keys, every pass in LDS: Per keys a
 // thread in registers, ranked wave by wave as in k_sort_scatter. A pass in
-// which all keys have one digit moves nothing. Four thousand keys, 8 passes,
-// one block: 32 us instead of 24 launches (170 us with their gaps in a
-// captured graph).
+// which all keys have one digit moves nothing. A thousand keys, 8 passes: 14 us
+// instead of 24 launches (170 us with their gaps in a captured graph).
 constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / kWave;
 
@@ -498,8 +497,9 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint64_t *key_in
 // step, so that the wait is for log2 of a bracket's loads, not for the tiles'
 // number of them.
 //
-// Tiles of 2048 keys up to 64k keys (sort and merge 21 + 18 us at 64k, where
-// eight passes of two launches took 115), then of 4096 (at 100k the merge takes
+// Tiles of 1024 keys up to 16k keys (sort and merge 14 + 13 us at 4096, where
+// one block takes 32), of 2048 up to 64k (21 + 18 us at 64k, where eight passes
+// of two launches took 115), then of 4096 (at 100k the merge takes
 // 30 us instead of 47; the passes took 130). The merge grows with
 // the square of the number of keys, which ends its range at kMergeMax.
 constexpr int kMergeSplit = 4;
@@ -1270,7 +1270,8 @@ int64_t sort_ws_bytes(int64_t n) {
 
 void radix_sort(uint64_t **key, uint32_t **val, uint64_t **key_alt, uint32_t **val_alt, int64_t n,
                 int passes, void *ws, hipStream_t s, const int64_t *n_dev) {
-    if (n <= kOneThreads * 8) {  // one block; the result where the passes would end
+    // one block; the result where the passes would end
+    if (n <= kOneThreads * (passes > 1 ? 2 : 8)) {
         uint64_t *ko = passes % 2 ? *key_alt : *key;
         uint32_t *vo = passes % 2 ? *val_alt : *val;
 #define SORT_ONE(Per)                                                                          \
@@ -1306,7 +1307,9 @@ void radix_sort(uint64_t **key, uint32_t **val, uint64_t **key_alt, uint32_t **v
     hipLaunchKernelGGL(k_sort_merge<Per>, dim3((unsigned)((n + kMergeKeys - 1) / kMergeKeys)), \
                        dim3(kOneThreads), 0, s, (const uint64_t *)kt, (const uint32_t *)vt,    \
                        ko, vo, (int)n, n_dev)
-        if (n <= kMergeTiles * 2 * kOneThreads) {
+        if (n <= kMergeTiles / 2 * kOneThreads) {
+            SORT_TILES(1);
+        } else if (n <= kMergeTiles * 2 * kOneThreads) {
             SORT_TILES(2);
         } else {
             SORT_TILES(4);
