@@ -1030,11 +1030,8 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     fill_words({{ptr<uint32_t>(ctx->status), 2 * kStatusForceWords}, {queue, kQueueWords}}, s);
     launch_gather_radii(a.r_in, a.r_out, a.r_search, t, st, s);
     launch_rsmax(t, s);
-    launch_group_flags(pre, t, a.group_size, ptr<uint32_t>(ctx->gflag), s);
-    scan_classes(ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos), n_nodes, &st->n_big,
-                 ptr<int64_t>(ctx->scan_ws), s);
-    launch_group_compact(pre, t, ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos),
-                         ptr<uint32_t>(ctx->groups), st, s);
+    launch_groups(pre, t, a.group_size, ptr<uint32_t>(ctx->gflag), ptr<uint32_t>(ctx->gpos),
+                  ptr<uint32_t>(ctx->groups), st, ptr<int64_t>(ctx->scan_ws), s);
     const uint32_t *tpos = nullptr, *tidx = nullptr;
     if (ctx->target) {  // targets of each group: a compacted list in Morton order
         launch_target_flags(ctx->target, t, ptr<uint32_t>(ctx->tflag), a.acc, a.pot, s);

@@ -49,7 +49,7 @@ struct Status {
     int32_t stack_overflow;  // walk stack exceeded its capacity
     unsigned long long inter[3];  // pc, far, near interactions
     int64_t n_groups;
-    int64_t n_big;           // of them, those listed first (see launch_group_flags)
+    int64_t n_big;           // of them, those listed first (see launch_groups)
     int64_t nb_total;        // neighbour-list entries (in the host's copy only)
     uint32_t rec_used[2];    // near-leaf hand-over claimed: headers, leaf entries (host)
     int64_t nb_rows;         // scratch entries the neighbour rows need (host)

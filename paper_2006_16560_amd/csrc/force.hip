@@ -1498,6 +1498,9 @@ void launch_team(const ForceLaunch &f, hipStream_t s) {
 //   teams of 4     0.054  0.092  0.153  0.306  0.806  1.92   3.93   8.28
 //   teams of 8     0.047  0.061  0.112  0.302  0.938  2.14   4.63   9.65
 //   teams of 16    0.039  0.050  0.160  0.559
+// (Taken before the large groups were listed first: since then the kernel in
+// use takes 0.093 at 16k, 0.266 at 64k, 0.758 at 200k and 1.88 at 500k; teams
+// of 8 take 0.292 at 64k and 0.441 at 100k, where teams of 4 take 0.398.)
 template <typename R, int IPL>
 void launch_t(const ForceLaunch &f, int resident_waves, hipStream_t s) {
     if constexpr (IPL <= 2) {

@@ -116,13 +116,10 @@ void launch_moments(const TreeDev &t, int levels, int n_sys, hipStream_t s);
 void launch_gather_radii(const double *r_in, const double *r_out, const double *r_search,
                          TreeDev t, Status *st, hipStream_t s);
 void launch_rsmax(const TreeDev &t, hipStream_t s);
-// flag[] is written for every slot up to t.n_nodes (the capacity): 0 for a cell
-// that is no group (and past the cells), 1 or, with more than half of
-// group_size particles, 2. The groups are listed with the twos first.
-void launch_group_flags(const PreOrder &pre, const TreeDev &t, int group_size, uint32_t *flag,
-                        hipStream_t s);
-void launch_group_compact(const PreOrder &pre, const TreeDev &t, const uint32_t *flag,
-                          const uint32_t *pos, uint32_t *groups, Status *st, hipStream_t s);
+// i-groups, those with more than half of group_size particles first; their
+// numbers into st. flag, pos: t.n_nodes (the capacity) + 1 words of scratch.
+void launch_groups(const PreOrder &pre, const TreeDev &t, int group_size, uint32_t *flag,
+                   uint32_t *pos, uint32_t *groups, Status *st, int64_t *ws, hipStream_t s);
 
 // changeover radii (eq. rcut / eq. rnb)
 void launch_changeover_radii(const double *mass, const double *vel, int64_t n, double rin_ref,

@@ -1144,22 +1144,21 @@ __global__ __launch_bounds__(kThreads) void k_rsmax(TreeDev t) {
 // kernel, 64k 0.31 -> 0.27 ms, 200k 0.82 -> 0.76, 300k at theta 0.3 3.37 ->
 // 3.31, FP64 64k 0.60 -> 0.51; a million stars and more as before. More classes
 // gave no more.)
+__device__ __forceinline__ uint32_t group_flag(const PreOrder &pre, int64_t c, int group_size) {
+    const uint4 info = pre.info[c];
+    const bool small = info.y <= (uint32_t)group_size || (info.z & kLeafFlag);
+    const uint32_t p = pre.parent[c];
+    const bool parent_big = p == kNone || pre.info[p].y > (uint32_t)group_size;
+    if (!small || !parent_big) return 0u;
+    return 2u * (uint64_t)info.y > (uint64_t)group_size ? 2u : 1u;
+}
+
 __global__ __launch_bounds__(kThreads) void k_group_flags(PreOrder pre, TreeDev t,
                                                           int group_size, uint32_t *flag) {
     const int64_t n_nodes = *t.n_nodes_dev;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < t.n_nodes;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        if (c >= n_nodes) {
-            flag[c] = 0u;
-            continue;
-        }
-        uint4 info = pre.info[c];
-        bool small = info.y <= (uint32_t)group_size || (info.z & kLeafFlag);
-        uint32_t p = pre.parent[c];
-        bool parent_big = p == kNone || pre.info[p].y > (uint32_t)group_size;
-        flag[c] = (small && parent_big) ? (2u * (uint64_t)info.y > (uint64_t)group_size ? 2u : 1u)
-                                        : 0u;
-    }
+         c += (int64_t)gridDim.x * blockDim.x)
+        flag[c] = c < n_nodes ? group_flag(pre, c, group_size) : 0u;
 }
 
 // Groups listed in pre-order (= Morton order of their particles), the large
@@ -1174,6 +1173,52 @@ __global__ __launch_bounds__(kThreads) void k_group_compact(PreOrder pre, TreeDe
          c += (int64_t)gridDim.x * blockDim.x)
         if (flag[c]) groups[pos[c] + (flag[c] == 2u ? 0u : n_big)] = pre.new_of_old[c];
     if (blockIdx.x == 0 && threadIdx.x == 0) st->n_groups = pos[t.n_nodes];
+}
+
+// Flags, positions and list of a tree of up to kGroupsOneMax cells by one
+// block, a run of cells a thread: 2.5 us at a thousand stars and 4.4 at 4096,
+// instead of 7 and 12 for three launches and their gaps.
+constexpr int kGroupsOneThreads = 1024;
+constexpr int kGroupsOnePer = 16;  // flags of a thread, two bits each
+constexpr int64_t kGroupsOneMax = kGroupsOneThreads * kGroupsOnePer;
+__global__ __launch_bounds__(kGroupsOneThreads) void k_groups_one(PreOrder pre, TreeDev t,
+                                                                  int group_size,
+                                                                  uint32_t *groups, Status *st) {
+    __shared__ uint32_t sum[kGroupsOneThreads / kWave][2];
+    const int64_t n_nodes = *t.n_nodes_dev < t.n_nodes ? *t.n_nodes_dev : t.n_nodes;
+    const int per = (int)((n_nodes + kGroupsOneThreads - 1) / kGroupsOneThreads);
+    const int64_t c0 = (int64_t)threadIdx.x * per;
+    uint32_t flags = 0, ones = 0, twos = 0;
+    for (int k = 0; k < per; k++) {
+        const uint32_t v = c0 + k < n_nodes ? group_flag(pre, c0 + k, group_size) : 0u;
+        flags |= v << (2 * k);
+        ones += v & 1u;
+        twos += v >> 1;
+    }
+    const uint32_t incl1 = wave_incl_scan(ones), incl2 = wave_incl_scan(twos);
+    const int w = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) {
+        sum[w][0] = incl1;
+        sum[w][1] = incl2;
+    }
+    __syncthreads();
+    uint32_t big = incl2 - twos, rest = incl1 - ones, n_big = 0, n_rest = 0;
+    for (int q = 0; q < kGroupsOneThreads / kWave; q++) {
+        if (q < w) {
+            rest += sum[q][0];
+            big += sum[q][1];
+        }
+        n_rest += sum[q][0];
+        n_big += sum[q][1];
+    }
+    for (int k = 0; k < per; k++) {
+        const uint32_t v = flags >> (2 * k) & 3u;
+        if (v) groups[v == 2u ? big++ : n_big + rest++] = pre.new_of_old[c0 + k];
+    }
+    if (threadIdx.x == 0) {
+        st->n_big = n_big;
+        st->n_groups = (int64_t)n_big + n_rest;
+    }
 }
 
 // ------------------------------------------------------- changeover radii
@@ -1419,16 +1464,18 @@ void launch_rsmax(const TreeDev &t, hipStream_t s) {
                        t);
 }
 
-void launch_group_flags(const PreOrder &pre, const TreeDev &t, int group_size, uint32_t *flag,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(k_group_flags, dim3(grid_for(t.n_nodes)), dim3(kThreads), 0, s, pre, t,
-                       group_size, flag);
-}
-
-void launch_group_compact(const PreOrder &pre, const TreeDev &t, const uint32_t *flag,
-                          const uint32_t *pos, uint32_t *groups, Status *st, hipStream_t s) {
-    hipLaunchKernelGGL(k_group_compact, dim3(grid_for(t.n_nodes)), dim3(kThreads), 0, s, pre, t,
-                       flag, pos, groups, st);
+void launch_groups(const PreOrder &pre, const TreeDev &t, int group_size, uint32_t *flag,
+                   uint32_t *pos, uint32_t *groups, Status *st, int64_t *ws, hipStream_t s) {
+    if (t.n_nodes <= kGroupsOneMax) {
+        hipLaunchKernelGGL(k_groups_one, dim3(1), dim3(kGroupsOneThreads), 0, s, pre, t,
+                           group_size, groups, st);
+        return;
+    }
+    const dim3 g(grid_for(t.n_nodes)), b(kThreads);
+    hipLaunchKernelGGL(k_group_flags, g, b, 0, s, pre, t, group_size, flag);
+    scan_classes(flag, pos, t.n_nodes, &st->n_big, ws, s);
+    hipLaunchKernelGGL(k_group_compact, g, b, 0, s, pre, t, (const uint32_t *)flag,
+                       (const uint32_t *)pos, groups, st);
 }
 
 void launch_changeover_radii(const double *mass, const double *vel, int64_t n, double rin_ref,
