@@ -1070,11 +1070,15 @@ __global__ __launch_bounds__(kThreads) void k_moments_level(TreeDev t, int level
 }
 
 // Levels from..0 by one block, each after the one below it is written (the
-// block's waves share their L1, so a barrier is enough). The levels of a
-// small tree, and of any tree the few at the top, cost 2 to 3 us each here
-// and 6 to 9 us as launches.
-constexpr int kTopThreads = 512;       // 8 children of a cell in registers
-constexpr int64_t kSmallTree = 16384;  // cells
+// block's waves share their L1, so a barrier is enough). A level of up to 512
+// cells costs 2 to 3 us here and 6 to 9 us as a launch (4 in a graph), a larger
+// one more, since the rest of the chip is idle. So the block takes the top of
+// every tree, and all of one with at most kTopCells cells for each launch that
+// this saves. Build of 3200 cells, 5 launches: 0.168 ms by one block, 0.162 by
+// launches; of 1600: 0.133 and 0.141; of 16200: 0.296 and 0.199; a replayed step
+// with room for 10600 cells, 17 launches: 0.350 and 0.352.
+constexpr int kTopThreads = 512;  // 8 children of a cell in registers
+constexpr int64_t kTopCells = 640;
 __global__ __launch_bounds__(kTopThreads) void k_moments_top(TreeDev t, int from) {
     __shared__ uint32_t off[kMaxLevel + 2];
     if (threadIdx.x < kMaxLevel + 2) off[threadIdx.x] = t.level_off[threadIdx.x];
@@ -1177,9 +1181,10 @@ __global__ __launch_bounds__(kThreads) void k_group_compact(PreOrder pre, TreeDe
 
 // Flags, positions and list of a tree of up to kGroupsOneMax cells by one
 // block, a run of cells a thread: 2.5 us at a thousand stars and 4.4 at 4096,
-// instead of 7 and 12 for three launches and their gaps.
+// instead of 7 and 12 for three launches and their gaps. (With 16 cells a thread
+// the loads of a wave spread too far: 10 us more than three launches.)
 constexpr int kGroupsOneThreads = 1024;
-constexpr int kGroupsOnePer = 16;  // flags of a thread, two bits each
+constexpr int kGroupsOnePer = 8;  // flags of a thread, two bits each
 constexpr int64_t kGroupsOneMax = kGroupsOneThreads * kGroupsOnePer;
 __global__ __launch_bounds__(kGroupsOneThreads) void k_groups_one(PreOrder pre, TreeDev t,
                                                                   int group_size,
@@ -1441,11 +1446,11 @@ void launch_relayout(const uint32_t *perm, const uint64_t *lkey, PreOrder pre, c
 void launch_moments(const TreeDev &t, int levels, int n_sys, hipStream_t s) {
     hipLaunchKernelGGL(k_moments_leaves, dim3(grid_for(t.n_nodes, kThreads, 8192)), dim3(kThreads),
                        0, s, t);
-    // one block takes every level of a small tree, else the levels at the top
-    // that cannot hold more than 512 cells
-    int top = levels - 1;
-    if (t.n_nodes > kSmallTree)
-        for (top = -1; top + 1 < levels && ((int64_t)n_sys << (3 * (top + 1))) <= 512;) top++;
+    // one block takes the levels at the top that cannot hold more than 512 cells,
+    // or every level of a small tree
+    int top = -1;
+    while (top + 1 < levels && ((int64_t)n_sys << (3 * (top + 1))) <= 512) top++;
+    if (t.n_nodes <= kTopCells * (levels - 1 - top)) top = levels - 1;
     for (int l = levels - 1; l > top; l--)
         hipLaunchKernelGGL(k_moments_level, dim3(grid_for(t.n_nodes, kThreads, 1024)),
                            dim3(kThreads), 0, s, t, l);
