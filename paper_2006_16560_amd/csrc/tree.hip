@@ -499,13 +499,14 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint64_t *key_in
 //
 // Tiles of 1024 keys up to 16k keys (sort and merge 14 + 13 us at 4096, where
 // one block takes 32), of 2048 up to 64k (21 + 18 us at 64k, where eight passes
-// of two launches took 115), then of 4096 (at 100k the merge takes
-// 30 us instead of 47; the passes took 130). The merge grows with
-// the square of the number of keys, which ends its range at kMergeMax.
+// of two launches took 115), then of 4096 (at 100k the merge takes 30 us instead
+// of 47; the passes took 130). The merge grows with the square of the number of
+// keys, which ends its range at kMergeMax: build of 131k stars 0.236 ms against
+// 0.304 by passes, of 160k 0.293 and 0.311, of 196k 0.285 and 0.320.
 constexpr int kMergeSplit = 4;
 constexpr int kMergeKeys = kOneThreads / kMergeSplit;
 constexpr int kMergeFlight = 8;
-constexpr int kMergeTiles = 32;
+constexpr int kMergeTiles = 48;
 constexpr int64_t kMergeMax = (int64_t)kMergeTiles * 4 * kOneThreads;
 
 template <int Per>
@@ -612,9 +613,10 @@ __global__ __launch_bounds__(kThreads) void k_scatter_particles(const double *po
         ps[rank[i]] = make_double4(pos[i], pos[n + i], pos[2 * n + i], mass[i]);
 }
 
-// Both at once, by gathers: up to kGatherMax particles (16 MB of input) the
-// scattered reads come from the caches and a launch is saved.
-constexpr int64_t kGatherMax = 1 << 18;
+// Both at once, by gathers: up to kGatherMax particles (4 MB of input, an XCD's
+// L2) the scattered reads come from the caches and a launch is saved; at 262144
+// the build takes 0.332 ms with it and 0.323 with the two kernels.
+constexpr int64_t kGatherMax = 1 << 17;
 __global__ __launch_bounds__(kThreads) void k_gather_all(const double *pos, const double *mass,
                                                          const uint32_t *idx, int64_t n,
                                                          double4 *ps, uint32_t *orig,
@@ -1357,9 +1359,9 @@ void radix_sort(uint64_t **key, uint32_t **val, uint64_t **key_alt, uint32_t **v
     hipLaunchKernelGGL(k_sort_merge<Per>, dim3((unsigned)((n + kMergeKeys - 1) / kMergeKeys)), \
                        dim3(kOneThreads), 0, s, (const uint64_t *)kt, (const uint32_t *)vt,    \
                        ko, vo, (int)n, n_dev)
-        if (n <= kMergeTiles / 2 * kOneThreads) {
+        if (n <= 16 * kOneThreads) {
             SORT_TILES(1);
-        } else if (n <= kMergeTiles * 2 * kOneThreads) {
+        } else if (n <= 32 * 2 * kOneThreads) {
             SORT_TILES(2);
         } else {
             SORT_TILES(4);

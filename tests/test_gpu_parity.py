@@ -1533,8 +1533,8 @@ def test_filter_and_clusters_row_shapes(pt, orc, n):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("n", [1024, 1025, 2049, 8192, 8193, 16385, 131072, 131073, 262144,
-                               262145])
+@pytest.mark.parametrize("n", [1024, 1025, 2049, 8192, 8193, 16385, 131072, 131073, 196608,
+                               196609, 262144, 262145])
 def test_build_at_size_edges(pt, orc, n):
     """Star numbers around the lines between the build's kernels (one block,
     few tiles, many tiles), with stars at equal positions among them: tree
@@ -1634,7 +1634,8 @@ def test_large_groups_listed_first(pt, ctx, orc, n, leaf, group):
         assert not acc.any() and not pot.any()
 
 
-@pytest.mark.parametrize("n", [8192, 8193, 10240, 65536, 65537, 131071, 131072, 131073])
+@pytest.mark.parametrize("n", [2048, 2049, 8193, 16384, 16385, 65536, 65537, 131071, 131073,
+                               196608, 196609])
 @pytest.mark.parametrize("hubs", [1, 300, "third"])
 def test_members_sorted_at_size_edges(pt, ctx, orc, n, hubs):
     """The sort of the cluster members (stable, equal keys in runs from a few
