@@ -916,6 +916,17 @@ struct ForceArgs {
     double kick_dt = 0.0;
 };
 
+// Sets one of the capacities of the hand-over and the rows. A captured step
+// graph holds them as kernel arguments, so one that changes outdates it, also
+// where the buffer has the room already: its kernels would drop what the host
+// takes as written.
+template <typename T>
+void set_cap(petar_ctx *ctx, T &cap, T want) {
+    if (cap == want) return;
+    cap = want;
+    ctx->graph_stale = true;
+}
+
 petar_status alloc_force(petar_ctx *ctx, const ForceArgs &a) {
     const int64_t n = ctx->n, n_nodes = ctx->n_nodes;
     const int prec = ctx->params.precision, ipl = ctx->params.i_per_lane;
@@ -939,8 +950,8 @@ petar_status alloc_force(petar_ctx *ctx, const ForceArgs &a) {
             if (want < have) want = have;
             return (uint32_t)(want > 0xffffffffull ? 0xffffffffull : want);
         };
-        ctx->nbhead_cap = cap((uint64_t)n_nodes + 4096, ctx->nbhead_cap);
-        ctx->nbleaf_cap = cap((uint64_t)n * 2 + 4096, ctx->nbleaf_cap);
+        set_cap(ctx, ctx->nbhead_cap, cap((uint64_t)n_nodes + 4096, ctx->nbhead_cap));
+        set_cap(ctx, ctx->nbleaf_cap, cap((uint64_t)n * 2 + 4096, ctx->nbleaf_cap));
         TRY(ensure(ctx, ctx->nbhead, (size_t)ctx->nbhead_cap * sizeof(uint4)));
         TRY(ensure(ctx, ctx->nbleaf, (size_t)ctx->nbleaf_cap * sizeof(uint2)));
         // rows: a first guess of 32 entries a particle (no more than the
@@ -948,7 +959,7 @@ petar_status alloc_force(petar_ctx *ctx, const ForceArgs &a) {
         // what the previous call needed (finish_force grows it and redoes the
         // passes)
         const int64_t first = std::min<int64_t>(32 * n, a.nb->capacity) + 4096;
-        if (ctx->nbrows_cap < first) ctx->nbrows_cap = first;
+        set_cap(ctx, ctx->nbrows_cap, std::max(ctx->nbrows_cap, first));
         TRY(ensure(ctx, ctx->nbrowoff, (size_t)(n + 1) * 8));
         TRY(ensure(ctx, ctx->nbrows, (size_t)ctx->nbrows_cap * 4));
     }
@@ -1105,15 +1116,9 @@ petar_status finish_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, boo
             const int64_t cap_bytes = ctx->params.workspace_cap;
             const int64_t after = ctx->ws_bytes - (int64_t)ctx->nbrows.cap + want * 4;
             exact = want > limit || (cap_bytes > 0 && after > cap_bytes);
-            if (!exact) {
-                ctx->nbrows_cap = want;
-            } else if (a.nb->capacity + 4096 > ctx->nbrows_cap) {
-                ctx->nbrows_cap = a.nb->capacity + 4096;
-            }
-            if ((size_t)ctx->nbrows_cap * 4 > ctx->nbrows.cap) {
-                TRY(ensure(ctx, ctx->nbrows, (size_t)ctx->nbrows_cap * 4));
-                ctx->graph_stale = true;
-            }
+            set_cap(ctx, ctx->nbrows_cap,
+                    exact ? std::max(ctx->nbrows_cap, a.nb->capacity + 4096) : want);
+            TRY(ensure(ctx, ctx->nbrows, (size_t)ctx->nbrows_cap * 4));
         }
         if (outgrown || walk) {
             enqueue_nb(ctx, a.nb, s, timed, exact ? kExact : kRedo, walk);
@@ -1143,11 +1148,9 @@ petar_status finish_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, boo
             uint64_t want = (uint64_t)need + need / 4;
             return (uint32_t)(want > 0xffffffffull ? 0xffffffffull : want);
         };
-        if (used[0] > ctx->nbhead_cap || used[1] > ctx->nbleaf_cap) {  // grow for the next call
-            if (used[0] > ctx->nbhead_cap) ctx->nbhead_cap = grow(used[0]);
-            if (used[1] > ctx->nbleaf_cap) ctx->nbleaf_cap = grow(used[1]);
-            ctx->graph_stale = true;
-        }
+        // overflowed: grow for the next call
+        if (used[0] > ctx->nbhead_cap) set_cap(ctx, ctx->nbhead_cap, grow(used[0]));
+        if (used[1] > ctx->nbleaf_cap) set_cap(ctx, ctx->nbleaf_cap, grow(used[1]));
         // exact rows that do not fit hold more entries than the capacity
         a.nb->required = exact && h.nb_rows > ctx->nbrows_cap ? h.nb_rows : h.nb_total;
         ctx->stats.nb_total = a.nb->required;

@@ -1649,3 +1649,63 @@ def test_members_sorted_at_size_edges(pt, ctx, orc, n, hubs):
     assert np.array_equal(label.cpu().numpy(), l_ref)
     assert np.array_equal(cl.cpu().numpy(), cl_ref)
     assert np.array_equal(members.cpu().numpy(), m_ref)
+
+
+@pytest.mark.parametrize("what", ["handover", "rows"])
+def test_step_graph_after_larger_eager_call(pt, orc, what):
+    """The capacities of the near-leaf hand-over (2 N + 4096 leaves) and of the
+    neighbour rows (32 N + 4096 entries) grow with an eager call on a few more
+    particles in the same context, into room that the buffers have already. A
+    step captured before it whose replay then needs more than the captured
+    capacity and less than the grown one still gives complete lists."""
+    n, n2 = 2000, 2200
+    leaf, group = (1, 8) if what == "handover" else (8, 64)
+    c = workloads.make_cluster(n2, 44, imf=True)
+    first = (np.ascontiguousarray(c.pos[:, :n]), c.mass[:n].copy())
+    rin, rout, few = (np.full(n2, r) for r in (1e-7, 1e-6, 1e-5))
+    cap = 64 * n2
+    eager = pt.petar_create(0)
+    pt.petar_set_params(eager, record_counts=1)
+
+    def needs(r):
+        """Near leaves handed over (leaf size 1) and row entries."""
+        pt.petar_tree_build(eager, T(first[0]), T(first[1]), 0.5, leaf)
+        pt.petar_force_long(eager, group, T(rin[:n]), T(rout[:n]), T(np.full(n, r)))
+        cnt = pt.petar_copy_counts(eager).cpu().numpy().astype(np.float64)
+        return (cnt[2] / cnt[3]).sum() if what == "handover" else cnt[2].sum()
+
+    lo_need, hi_need = (2 * n + 4096, 2 * n2 + 4096) if what == "handover" else \
+        (32 * n + 4096, 32 * n2 + 4096)
+    lo, hi = 1e-5, 1.0
+    for _ in range(60):
+        many = 0.5 * (lo + hi)
+        need = needs(many)
+        if need <= lo_need + 20:
+            lo = many
+        elif need >= hi_need - 20:
+            hi = many
+        else:
+            break
+    assert lo_need + 20 < need < hi_need - 20
+    pt.petar_destroy(eager)
+    o_ref, i_ref = orc.neighbours(first[0], np.full(n, many))
+    assert o_ref[-1] <= cap
+
+    ctx = pt.petar_create(0)
+    args = [T(first[0]), T(first[1]), 0.5, leaf, group, T(rin[:n]), T(rout[:n]), T(few[:n]),
+            torch.empty((3, n), dtype=torch.float64, device="cuda:0"),
+            torch.empty(n, dtype=torch.float64, device="cuda:0")]
+    nb = (torch.empty(n + 1, dtype=torch.int64, device="cuda:0"),
+          torch.empty(cap, dtype=torch.int32, device="cuda:0"))
+    for _ in range(2):
+        pt.petar_step_graph(ctx, *args, nb=nb)
+    before = pt.petar_get_stats(ctx)["workspace_bytes"]
+    pt.petar_tree_build(ctx, T(c.pos), T(c.mass), 0.5, leaf)
+    pt.petar_force_long(ctx, group, T(rin), T(rout), T(few), nb_capacity=cap)
+    assert pt.petar_get_stats(ctx)["workspace_bytes"] == before  # no buffer has moved
+    args[7].copy_(T(np.full(n, many)))
+    for _ in range(3):
+        tot = pt.petar_step_graph(ctx, *args, nb=nb)
+        assert tot == o_ref[-1] and np.array_equal(nb[0].cpu().numpy(), o_ref)
+        assert np.array_equal(nb[1][:tot].cpu().numpy(), i_ref)
+    pt.petar_destroy(ctx)
