@@ -840,14 +840,17 @@ void enqueue_build_b(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int d
     uint64_t *lk = ptr<uint64_t>(ctx->lkey0), *lka = ptr<uint64_t>(ctx->lkey1);
     uint32_t *lv = ptr<uint32_t>(ctx->lval0), *lva = ptr<uint32_t>(ctx->lval1);
     const uint64_t *k = ptr<uint64_t>(ctx->key0);
-    launch_octree_write(k, a.n, a.leaf_size, levels, ptr<int64_t>(ctx->base), pre, lk, lv,
+    const RootBox *rb = ptr<RootBox>(ctx->rootbox);
+    launch_octree_write(k, a.n, a.leaf_size, levels, ptr<int64_t>(ctx->base), rb, pre, lk, lv,
                         node_cap, st, s);
     radix_sort(&lk, &lv, &lka, &lva, node_cap, 1, ctx->sort_ws.p, s,
                t.n_nodes_dev);
-    launch_relayout(lv, lk, pre, ptr<RootBox>(ctx->rootbox), k, levels, t,
-                    ptr<uint32_t>(ctx->level_off), st, leaf_slots(ctx), s);
+    launch_relayout(lv, lk, pre, rb, k, levels, t, ptr<uint32_t>(ctx->level_off), st,
+                    leaf_slots(ctx), s);
     launch_moments(t, deep, a.n_sys > 0 ? a.n_sys : 1, s);
 }
+
+const char kBadInput[] = "non-finite position or mass, or negative mass";
 
 void set_tree_state(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int deep) {
     ctx->n = a.n;
@@ -879,8 +882,7 @@ petar_status build_eager(petar_ctx *ctx, const BuildArgs &a) {
     enqueue_build_a(ctx, a, s, true);
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(s));  // cell count, input check, deepest level
-    if (ctx->host_scalar[1])
-        return fail(ctx, PETAR_E_INVALID, "non-finite position or mass, or negative mass");
+    if (ctx->host_scalar[1]) return fail(ctx, PETAR_E_INVALID, kBadInput);
     const int64_t n_nodes = ctx->host_scalar[0];
     if (n_nodes < 1 || n_nodes >= (int64_t)kNone)
         return fail(ctx, PETAR_E_INTERNAL, "cell count %lld out of range", (long long)n_nodes);
@@ -1096,8 +1098,9 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
 petar_status finish_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed) {
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    TRY(settle_build_stats(ctx, true));
     const Status &h = *ctx->host_status;
+    if (h.bad_input) return fail(ctx, PETAR_E_INVALID, kBadInput);  // of a replayed step
+    TRY(settle_build_stats(ctx, true));
     bool exact = false;
     if (a.nb && !h.invalid_radii && !h.stack_overflow && !h.cell_overflow) {
         // the hand-over overflowed: the passes run by a walk of their own
@@ -1320,11 +1323,13 @@ petar_status petar_step_graph(petar_ctx *ctx, int n_sys, const int64_t *sys_offs
     hipStream_t s = ctx->stream;
     set_tree_state(ctx, ba, ctx->node_cap, ba.n_sys > 0 ? kBatchLevels : kMaxLevel);
     ctx->have_tree = false;
+    ctx->have_counts = false;
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], s));
     HIP_TRY(ctx, hipGraphLaunch(ctx->gexec, s));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], s));
     petar_status st = finish_force(ctx, fa, s, false);
     const Status &h = *ctx->host_status;
+    if (h.bad_input) return st;
     if (h.cell_overflow) {  // tree outgrew the captured capacity: redo eagerly, recapture next
         ctx->graph_stale = true;
         TRY(build_eager(ctx, ba));

@@ -54,8 +54,9 @@ struct Status {
     uint32_t rec_used[2];    // near-leaf hand-over claimed: headers, leaf entries (host)
     int64_t nb_rows;         // scratch entries the neighbour rows need (host)
     // build
-    int32_t cell_overflow;   // more cells than the preallocated capacity (captured graphs)
-    int32_t pad;
+    int32_t cell_overflow;   // no cells: more than the preallocated capacity (captured
+                             // graphs), or bad_input
+    int32_t bad_input;       // non-finite or negative input (the root box's count)
     int64_t n_nodes;
     int64_t n_leaves;
     int64_t max_level;

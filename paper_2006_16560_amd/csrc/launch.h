@@ -98,11 +98,12 @@ void launch_octree_count(const uint64_t *key, int64_t n, int leaf_size, int leve
 void launch_build_head(const int64_t *base, int64_t n, const RootBox *rb,
                        const uint32_t *deep_slots, int64_t *host, hipStream_t s);
 // Pre-order cells; also the level keys (lkey, lval) sorted next.
-// st->n_nodes = cells; more than node_cap are not written, but
-// st->cell_overflow is raised and st->n_nodes = 0.
+// st->n_nodes = cells; more than node_cap, or those of bad input (rb->bad,
+// passed on in st->bad_input), are not written, but st->cell_overflow is
+// raised and st->n_nodes = 0.
 void launch_octree_write(const uint64_t *key, int64_t n, int leaf_size, int levels,
-                         const int64_t *base, PreOrder pre, uint64_t *lkey, uint32_t *lval,
-                         int64_t node_cap, Status *st, hipStream_t s);
+                         const int64_t *base, const RootBox *rb, PreOrder pre, uint64_t *lkey,
+                         uint32_t *lval, int64_t node_cap, Status *st, hipStream_t s);
 // Level-order arrays from the level-sorted permutation perm (new -> old).
 // rb holds one root box per system (one in single-system mode); lkey are the
 // sorted levels. Also the deepest level into st and the leaves, spread over

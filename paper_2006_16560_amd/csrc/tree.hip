@@ -778,17 +778,21 @@ __global__ __launch_bounds__(kThreads) void k_octree_count(const uint64_t *key, 
 // keys), so that no thread walks a whole root-to-leaf chain of searches.
 __global__ __launch_bounds__(kThreads) void k_octree_emit(const uint64_t *key, int64_t n,
                                                           int levels, const int64_t *base,
-                                                          PreOrder pre, int64_t node_cap,
-                                                          Status *st) {
+                                                          const RootBox *rb, PreOrder pre,
+                                                          int64_t node_cap, Status *st) {
     // device cell count for the build's second half: the scanned count, or 0
     // (with Status::cell_overflow raised) when it exceeds the arrays'
-    // capacity, so that every later kernel does nothing
+    // capacity or the input is bad (in a captured step nobody has looked yet),
+    // so that every later kernel does nothing
     const int64_t cells = base[n];
+    const int bad = rb->bad;
+    const bool none = cells > node_cap || bad != 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->n_nodes = cells > node_cap ? 0 : cells;
-        if (cells > node_cap) st->cell_overflow = 1;
+        st->n_nodes = none ? 0 : cells;
+        if (none) st->cell_overflow = 1;
+        st->bad_input = bad;
     }
-    if (cells > node_cap) return;
+    if (none) return;
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b = base[k];
@@ -1428,10 +1432,10 @@ void launch_build_head(const int64_t *base, int64_t n, const RootBox *rb,
 }
 
 void launch_octree_write(const uint64_t *key, int64_t n, int leaf_size, int levels,
-                         const int64_t *base, PreOrder pre, uint64_t *lkey, uint32_t *lval,
-                         int64_t node_cap, Status *st, hipStream_t s) {
+                         const int64_t *base, const RootBox *rb, PreOrder pre, uint64_t *lkey,
+                         uint32_t *lval, int64_t node_cap, Status *st, hipStream_t s) {
     hipLaunchKernelGGL(k_octree_emit, dim3(grid_for(n)), dim3(kThreads), 0, s, key, n, levels,
-                       base, pre, node_cap, st);
+                       base, rb, pre, node_cap, st);
     hipLaunchKernelGGL(k_octree_write, dim3(grid_for(node_cap)), dim3(kThreads), 0, s, key, n,
                        leaf_size, levels, base, pre, lkey, lval, (const Status *)st);
 }

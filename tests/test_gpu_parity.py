@@ -1709,3 +1709,49 @@ def test_step_graph_after_larger_eager_call(pt, orc, what):
         assert tot == o_ref[-1] and np.array_equal(nb[0].cpu().numpy(), o_ref)
         assert np.array_equal(nb[1][:tot].cpu().numpy(), i_ref)
     pt.petar_destroy(ctx)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_step_graph_replay_refuses_bad_input(pt, orc, batch):
+    """A replayed step refuses what the eager build refuses, a position or mass
+    that is not finite or a negative mass (in any system of a batch), leaves
+    no tree and no counts behind, and gives the first results again once the
+    input is restored."""
+    n = 3000
+    c, rin, rout, rs = cluster_with_radii(orc, n, 45)
+    off = [0, 1000, 1001, n] if batch else None
+    dpos, dmass = T(c.pos), T(c.mass)
+    radii = [T(rin), T(rout), T(rs)]
+    acc = torch.empty((3, n), dtype=torch.float64, device="cuda:0")
+    pot = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    nb = (torch.empty(n + 1, dtype=torch.int64, device="cuda:0"),
+          torch.empty(64 * n, dtype=torch.int32, device="cuda:0"))
+    ctx = pt.petar_create(0)
+    pt.petar_set_params(ctx, record_counts=1)
+
+    def step():
+        tot = pt.petar_step_graph(ctx, dpos, dmass, 0.5, 8, 64, *radii, acc, pot, sys_offsets=off,
+                                  nb=nb)
+        return [acc.clone(), pot.clone(), nb[0].clone(), nb[1][:tot].clone()]
+
+    want = step()
+    for array, where, value in ((dpos, (1, n - 1), float("nan")), (dpos, (0, 5), float("inf")),
+                                (dmass, (n - 1,), -1.0), (dmass, (0,), float("nan")),
+                                (dmass, (1000,), float("-inf"))):
+        keep = array[where].item()
+        array[where] = value
+        with pytest.raises(pt.PetarError) as e:
+            step()
+        assert e.value.status == pt.PETAR_E_INVALID and "non-finite" in str(e.value)
+        with pytest.raises(pt.PetarError) as e:
+            pt.petar_force_long(ctx, 64, *radii)
+        assert e.value.status == pt.PETAR_E_STATE
+        with pytest.raises(pt.PetarError) as e:
+            pt.petar_copy_counts(ctx)
+        assert e.value.status == pt.PETAR_E_STATE
+        array[where] = keep
+        got = step()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        assert pt.petar_get_stats(ctx)["ms_graph"] > 0.0  # replayed
+        pt.petar_force_long(ctx, 64, *radii)
+    pt.petar_destroy(ctx)
