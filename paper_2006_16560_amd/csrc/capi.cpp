@@ -74,6 +74,8 @@ struct petar_ctx {
     int deep = kMaxLevel;  // deepest cell level: the per-level passes start above it
     bool build_stats_pending = false;  // eager build not yet read back (see settle_build_stats)
     int n_sys = 1;
+    int64_t sys_off_host[kMaxSystemsHost + 1];  // what sys_off holds, of sys_off_n systems
+    int sys_off_n = 0;
 
     int force_waves[2][5] = {{0}};
     int nb_waves = 0;
@@ -862,10 +864,15 @@ void set_tree_state(petar_ctx *ctx, const BuildArgs &a, int64_t node_cap, int de
     ctx->n_sys = a.n_sys > 0 ? a.n_sys : 1;
 }
 
+// The offsets of a batch to the device. A captured step reads them there, so
+// a replay brings its own back after a build of another batch.
 petar_status copy_offsets(petar_ctx *ctx, const BuildArgs &a, hipStream_t s) {
-    if (a.n_sys > 0)
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->sys_off.p, a.sys_off, (size_t)(a.n_sys + 1) * 8,
+    if (a.n_sys > 0) {
+        ctx->sys_off_n = a.n_sys;
+        std::copy(a.sys_off, a.sys_off + a.n_sys + 1, ctx->sys_off_host);
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->sys_off.p, ctx->sys_off_host, (size_t)(a.n_sys + 1) * 8,
                                     hipMemcpyHostToDevice, s));
+    }
     return PETAR_OK;
 }
 
@@ -1324,6 +1331,9 @@ petar_status petar_step_graph(petar_ctx *ctx, int n_sys, const int64_t *sys_offs
     set_tree_state(ctx, ba, ctx->node_cap, ba.n_sys > 0 ? kBatchLevels : kMaxLevel);
     ctx->have_tree = false;
     ctx->have_counts = false;
+    if (n_sys > 0 && (ctx->sys_off_n != n_sys ||
+                      !std::equal(sys_offsets, sys_offsets + n_sys + 1, ctx->sys_off_host)))
+        TRY(copy_offsets(ctx, ba, s));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], s));
     HIP_TRY(ctx, hipGraphLaunch(ctx->gexec, s));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], s));

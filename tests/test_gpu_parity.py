@@ -1755,3 +1755,33 @@ def test_step_graph_replay_refuses_bad_input(pt, orc, batch):
         assert pt.petar_get_stats(ctx)["ms_graph"] > 0.0  # replayed
         pt.petar_force_long(ctx, 64, *radii)
     pt.petar_destroy(ctx)
+
+
+def test_step_graph_after_build_of_other_batch(pt, orc):
+    """A captured step of a batch reads the systems' offsets on the device: a
+    replay after a build of another batch (as many systems, then fewer) of as
+    many particles still takes its own."""
+    n = 2048  # the other batches need no more scratch: the graph stays
+    c, rin, rout, rs = cluster_with_radii(orc, n, 46)
+    off = [0, 1000, 1500, 2047, n]
+    dpos, dmass = T(c.pos), T(c.mass)
+    radii = [T(rin), T(rout), T(rs)]
+    acc = torch.empty((3, n), dtype=torch.float64, device="cuda:0")
+    pot = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    nb = (torch.empty(n + 1, dtype=torch.int64, device="cuda:0"),
+          torch.empty(64 * n, dtype=torch.int32, device="cuda:0"))
+    ctx = pt.petar_create(0)
+
+    def step():
+        tot = pt.petar_step_graph(ctx, dpos, dmass, 0.5, 8, 64, *radii, acc, pot, sys_offsets=off,
+                                  nb=nb)
+        return [acc.clone(), pot.clone(), nb[0].clone(), nb[1][:tot].clone()]
+
+    want = step()
+    for other in (None, [0, 700, 701, 1300, n], [0, 1, n]):
+        if other:
+            pt.petar_batch_build(ctx, other, dpos, dmass, 0.5, 8)
+        got = step()
+        assert pt.petar_get_stats(ctx)["ms_graph"] > 0.0  # replayed
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    pt.petar_destroy(ctx)
