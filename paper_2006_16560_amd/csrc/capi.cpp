@@ -195,9 +195,11 @@ TreeDev tree_view(petar_ctx *c) {
     return t;
 }
 
-// Words behind the emit counts: the deepest level's slots, each followed by
-// the leaves' slot.
-uint32_t *deep_slots(petar_ctx *c) { return ptr<uint32_t>(c->emit) + c->n; }
+// Words behind the status words: the deepest level's slots, each followed by
+// the leaves' slot. (The status is read after builds that failed too, so they
+// must not move with the number of particles.)
+constexpr size_t kStatusBytes = (sizeof(Status) + 127) / 128 * 128;
+uint32_t *deep_slots(petar_ctx *c) { return ptr<uint32_t>(c->status) + kStatusBytes / 4; }
 uint32_t *leaf_slots(petar_ctx *c) { return deep_slots(c) + 1; }
 
 petar_status read_status(petar_ctx *c, hipStream_t s) {
@@ -766,8 +768,8 @@ petar_status alloc_build_a(petar_ctx *ctx, const BuildArgs &a) {
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_need * 8));
     TRY(ensure(ctx, ctx->bbox_part, (size_t)bbox_partial_blocks(a.n, n_boxes) * 6 * 8));
     TRY(ensure(ctx, ctx->rootbox, sizeof(RootBox) * (size_t)n_boxes));
-    TRY(ensure(ctx, ctx->status, sizeof(Status)));
-    TRY(ensure(ctx, ctx->emit, (N + kDeepWords) * 4));  // + the deepest-level words
+    TRY(ensure(ctx, ctx->status, kStatusBytes + kDeepWords * 4));
+    TRY(ensure(ctx, ctx->emit, N * 4));
     TRY(ensure(ctx, ctx->base, (N + 1) * 8));
     TRY(ensure(ctx, ctx->ps, N * sizeof(double4)));
     TRY(ensure(ctx, ctx->orig, N * 4));
@@ -806,9 +808,8 @@ void enqueue_build_a(petar_ctx *ctx, const BuildArgs &a, hipStream_t s, bool hea
     const int levels = a.n_sys > 0 ? kBatchLevels : kMaxLevel;
     RootBox *rb = ptr<RootBox>(ctx->rootbox);
     uint32_t *deep = deep_slots(ctx);
-    fill_words({{ptr<uint32_t>(ctx->status), (int64_t)(sizeof(Status) / 4)},
-                {ptr<uint32_t>(ctx->rootbox), (int64_t)(sizeof(RootBox) / 4) * n_boxes},
-                {deep, kDeepWords}},
+    fill_words({{ptr<uint32_t>(ctx->status), (int64_t)(kStatusBytes / 4) + kDeepWords},
+                {ptr<uint32_t>(ctx->rootbox), (int64_t)(sizeof(RootBox) / 4) * n_boxes}},
                s);
     uint64_t *k = ptr<uint64_t>(ctx->key0), *ka = ptr<uint64_t>(ctx->key1);
     uint32_t *v = ptr<uint32_t>(ctx->val0), *va = ptr<uint32_t>(ctx->val1);

@@ -1785,3 +1785,32 @@ def test_step_graph_after_build_of_other_batch(pt, orc):
         assert pt.petar_get_stats(ctx)["ms_graph"] > 0.0  # replayed
         assert all(torch.equal(a, b) for a, b in zip(got, want))
     pt.petar_destroy(ctx)
+
+
+def test_stats_after_failed_build(pt, orc):
+    """The counters of a build whose second half is still queued are read with
+    the next petar_get_stats, also when a build of many more particles has
+    failed in between at the workspace cap, for want of any of its buffers."""
+    c = workloads.make_cluster(2000, 47)
+    dpos, dmass = T(c.pos), T(c.mass)
+    big = workloads.make_cluster(300000, 48)
+    bpos, bmass = T(big.pos), T(big.mass)
+    ref = orc.tree_info(c.pos, c.mass, 8, 64)
+    for per_star in (0, 9, 20, 28, 33, 40, 72, 80):  # bytes of room for a larger star number
+        ctx = pt.petar_create(0)
+        pt.petar_tree_build(ctx, dpos, dmass, 0.5, 8)
+        used = pt.petar_get_stats(ctx)["workspace_bytes"]
+        pt.petar_tree_build(ctx, dpos, dmass, 0.5, 8)
+        pt.petar_set_params(ctx, workspace_cap=used + per_star * 300000)
+        with pytest.raises(pt.PetarError) as e:
+            pt.petar_tree_build(ctx, bpos, bmass, 0.5, 8)
+        assert e.value.status == pt.PETAR_E_NOMEM
+        st = pt.petar_get_stats(ctx)
+        assert st["n"] == 2000 and st["n_nodes"] == ref["n_cells"]
+        if per_star <= 72:  # the build failed before its first launch
+            assert (st["n_leaves"], st["max_level"]) == (ref["n_leaves"], ref["max_level"])
+        pt.petar_set_params(ctx, workspace_cap=0)
+        pt.petar_tree_build(ctx, dpos, dmass, 0.5, 8)
+        st = pt.petar_get_stats(ctx)
+        assert (st["n_leaves"], st["max_level"]) == (ref["n_leaves"], ref["max_level"])
+        pt.petar_destroy(ctx)
