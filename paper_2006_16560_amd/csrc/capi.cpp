@@ -55,6 +55,7 @@ struct petar_ctx {
     // artificial particles
     DevBuf art_single, art_spos, art_status, art_pairof, tt_ginv, grp_off, grp_idx;
     bool tt_ginv_ready = false;
+    bool lists_in_use = false;  // cl_masks and grp_idx, by the call that runs
     uint32_t nbhead_cap = 0, nbleaf_cap = 0;
     int64_t nbrows_cap = 0;  // entries of nbrows; grown when a call's rows needed more
 
@@ -121,43 +122,77 @@ petar_status fail(petar_ctx *ctx, petar_status st, const char *fmt, ...) {
         if (s_ != PETAR_OK) return s_;     \
     } while (0)
 
-// Grows a device buffer to at least `bytes` (contents are not kept).
-petar_status ensure(petar_ctx *ctx, DevBuf &b, size_t bytes) {
-    if (bytes == 0) bytes = 8;
-    if (b.cap >= bytes) return PETAR_OK;
-    size_t want = bytes + bytes / 8;  // headroom against small growth
-    int64_t after = ctx->ws_bytes - (int64_t)b.cap + (int64_t)want;
-    if (ctx->params.workspace_cap > 0 && after > ctx->params.workspace_cap) {
-        want = bytes;
-        after = ctx->ws_bytes - (int64_t)b.cap + (int64_t)want;
-        if (after > ctx->params.workspace_cap)
-            return fail(ctx, PETAR_E_NOMEM, "workspace cap of %lld bytes exceeded (need %lld)",
-                        (long long)ctx->params.workspace_cap, (long long)after);
-    }
-    if (b.p) {
-        // work queued by an earlier call (the second half of a tree build)
-        // may still use the buffer
-        (void)hipStreamSynchronize(ctx->stream);
-        hipFree(b.p);
-        ctx->ws_bytes -= (int64_t)b.cap;
-        b.p = nullptr;
-        b.cap = 0;
-    }
-    ctx->graph_stale = true;  // a captured step graph may hold the old address
-    hipError_t e = hipMalloc(&b.p, want);
-    if (e != hipSuccess) {
-        b.p = nullptr;
-        return fail(ctx, PETAR_E_NOMEM, "hipMalloc(%zu) failed: %s", want, hipGetErrorString(e));
-    }
-    b.cap = want;
-    ctx->ws_bytes += (int64_t)want;
-    return PETAR_OK;
+void drop(petar_ctx *ctx, DevBuf &b) {
+    if (!b.p) return;
+    // work queued by an earlier call (the second half of a tree build) may
+    // still use the buffer
+    (void)hipStreamSynchronize(ctx->stream);
+    (void)hipFree(b.p);
+    ctx->ws_bytes -= (int64_t)b.cap;
+    b.p = nullptr;
+    b.cap = 0;
 }
 
-// Whether ensure(b, bytes) would stay below the workspace cap.
+// Whether a buffer of `bytes` in place of b stays below the workspace cap.
 bool room_for(petar_ctx *ctx, const DevBuf &b, size_t bytes) {
     return b.cap >= bytes || ctx->params.workspace_cap <= 0 ||
            ctx->ws_bytes - (int64_t)b.cap + (int64_t)bytes <= ctx->params.workspace_cap;
+}
+
+// `bytes` and an eighth against small growth, where there is room for it.
+size_t with_headroom(petar_ctx *ctx, const DevBuf &b, size_t bytes) {
+    return room_for(ctx, b, bytes + bytes / 8) ? bytes + bytes / 8 : bytes;
+}
+
+// A new buffer of `bytes` in place of b (contents are not kept).
+hipError_t replace(petar_ctx *ctx, DevBuf &b, size_t bytes) {
+    drop(ctx, b);
+    ctx->graph_stale = true;  // a captured step graph may hold the old address
+    const hipError_t e = hipMalloc(&b.p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        b.p = nullptr;
+        return e;
+    }
+    b.cap = bytes;
+    ctx->ws_bytes += (int64_t)bytes;
+    return hipSuccess;
+}
+
+// Frees scratch that only saves time (the filter's star records) and the
+// filter's other scratch while no filter or groups call uses it. Whether
+// there was any.
+bool give_way(petar_ctx *ctx) {
+    const int64_t before = ctx->ws_bytes;
+    drop(ctx, ctx->cl_rec);
+    if (!ctx->lists_in_use) {
+        drop(ctx, ctx->cl_masks);
+        drop(ctx, ctx->grp_idx);
+    }
+    return ctx->ws_bytes < before;
+}
+
+// Grows a device buffer to at least `bytes` (contents are not kept). Scratch
+// that can be spared gives way.
+petar_status ensure(petar_ctx *ctx, DevBuf &b, size_t bytes) {
+    if (bytes == 0) bytes = 8;
+    if (b.cap >= bytes) return PETAR_OK;
+    const size_t want = with_headroom(ctx, b, bytes);
+    if (!room_for(ctx, b, want) && !(give_way(ctx) && room_for(ctx, b, want)))
+        return fail(ctx, PETAR_E_NOMEM, "workspace cap of %lld bytes exceeded (need %lld)",
+                    (long long)ctx->params.workspace_cap,
+                    (long long)(ctx->ws_bytes - (int64_t)b.cap + (int64_t)want));
+    hipError_t e = replace(ctx, b, want);
+    if (e != hipSuccess && give_way(ctx)) e = replace(ctx, b, want);
+    if (e != hipSuccess)
+        return fail(ctx, PETAR_E_NOMEM, "hipMalloc(%zu) failed: %s", want, hipGetErrorString(e));
+    return PETAR_OK;
+}
+
+// Grows a buffer that a call can do without; whether it has `bytes` now.
+bool try_grow(petar_ctx *ctx, DevBuf &b, size_t bytes) {
+    return b.cap >= bytes || (room_for(ctx, b, bytes) &&
+                              replace(ctx, b, with_headroom(ctx, b, bytes)) == hipSuccess);
 }
 
 template <typename T>
@@ -379,6 +414,13 @@ petar_status petar_changeover_radii(petar_ctx *ctx, const double *mass, const do
 
 namespace {
 
+// Raises a flag for as long as it lives.
+struct InUse {
+    bool &flag;
+    explicit InUse(bool &f) : flag(f) { flag = true; }
+    ~InUse() { flag = false; }
+};
+
 // Filter of a candidate CSR (mode 0: pericentre, mode 1: group relation) into
 // out_offsets[n + 1] / out_idx[capacity]; *required = kept entries. With
 // out_idx null the entries go to grp_idx. One host read when the scratch of
@@ -392,21 +434,20 @@ petar_status filter_impl(petar_ctx *ctx, FilterArgs a, int64_t *out_offsets, int
     TRY(ensure(ctx, ctx->cl_status, 8));
     TRY(ensure(ctx, ctx->cl_counts, (size_t)(n + 1) * 4));
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_ws_elems(n + 1) * 8));
-    // records when there is room for them (they only save time)
-    double *rec = nullptr;
-    const size_t rec_bytes = (size_t)n * (size_t)filter_rec_doubles(a.mode) * 8;
-    if (room_for(ctx, ctx->cl_rec, rec_bytes)) {
-        TRY(ensure(ctx, ctx->cl_rec, rec_bytes));
-        rec = ptr<double>(ctx->cl_rec);
+    // first guesses: 16 candidates a star, 4 of them kept. Under a cap none: what
+    // they take beyond the need could be missed by a later call (then the passes
+    // run twice in the call that first meets a size).
+    if (ctx->params.workspace_cap <= 0) {
+        (void)try_grow(ctx, ctx->cl_masks, (size_t)filter_words(n, 16 * n) * 8);
+        if (own) (void)try_grow(ctx, ctx->grp_idx, (size_t)n * 16);
     }
-    // first guesses: 16 candidates a star, 4 of them kept
-    const size_t guess = (size_t)filter_words(n, 16 * n) * 8, guess_idx = (size_t)n * 16;
-    if (ctx->cl_masks.cap < guess && room_for(ctx, ctx->cl_masks, guess))
-        TRY(ensure(ctx, ctx->cl_masks, guess));
-    if (own && ctx->grp_idx.cap < guess_idx && room_for(ctx, ctx->grp_idx, guess_idx))
-        TRY(ensure(ctx, ctx->grp_idx, guess_idx));
+    const size_t rec_bytes = (size_t)n * (size_t)filter_rec_doubles(a.mode) * 8;
     int32_t *bad = ptr<int32_t>(ctx->cl_status), *csr_bad = bad + 1;
     while (true) {
+        // records where there is room for them: they only save time, and give
+        // way to whatever is needed later (see give_way)
+        double *rec =
+            try_grow(ctx, ctx->cl_rec, rec_bytes) ? ptr<double>(ctx->cl_rec) : nullptr;
         if (own) {
             out_idx = ptr<int32_t>(ctx->grp_idx);
             capacity = (int64_t)(ctx->grp_idx.cap / 4);
@@ -587,6 +628,7 @@ petar_status petar_nb_filter(petar_ctx *ctx, int64_t n, const double *pos, const
         return fail(ctx, PETAR_E_INVALID, "%s", m);
     if (ctx->device == PETAR_NO_DEVICE) return fail(ctx, PETAR_E_NODEVICE, "no device");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
+    InUse lists(ctx->lists_in_use);
     FilterArgs a{pos, vel, mass, r_nb, cand_offsets, cand_idx, n, c_v, ctx->params.G, 0};
     return filter_impl(ctx, a, out->offsets_dev, out->idx_dev, out->capacity, &out->required);
 }
@@ -604,6 +646,7 @@ petar_status petar_groups(petar_ctx *ctx, int64_t n, const double *pos, const do
     if (ctx->device == PETAR_NO_DEVICE) return fail(ctx, PETAR_E_NODEVICE, "no device");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
+    InUse lists(ctx->lists_in_use);
     TRY(ensure(ctx, ctx->grp_off, (size_t)(n + 1) * 8));
     FilterArgs a{pos, vel, mass, r_in, cand_offsets, cand_idx, n, theta, ctx->params.G, 1};
     int64_t kept = 0;

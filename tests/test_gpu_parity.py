@@ -1814,3 +1814,60 @@ def test_stats_after_failed_build(pt, orc):
         st = pt.petar_get_stats(ctx)
         assert (st["n_leaves"], st["max_level"]) == (ref["n_leaves"], ref["max_level"])
         pt.petar_destroy(ctx)
+
+
+def _short_lists(rng, n):
+    """A candidate CSR of 0 to 4 entries a row (2 on average)."""
+    offs = np.zeros(n + 1, dtype=np.int64)
+    offs[1:] = np.cumsum(rng.integers(0, 5, n))
+    return offs, rng.integers(0, n, offs[-1]).astype(np.int32)
+
+
+def test_workspace_cap_through_cluster_chain(pt, orc):
+    """What only saves time gives way to what a call needs: under one cap that
+    stays in force, with room for the scratch that petar_nb_filter,
+    petar_clusters, petar_groups (about 61 bytes a star here) and a build with
+    its force call need, but not for the filter's star records (64 bytes a
+    star) or its guesses beside it, the chain gives the results of a context
+    without a cap, twice over and in both orders."""
+    n = 50000
+    c, rin, rout, rs = cluster_with_radii(orc, n, 41, bf=0.3)
+    offs, idx = _short_lists(np.random.default_rng(41), n)
+    pos, vel, mass, doffs, didx = T(c.pos), T(c.vel), T(c.mass), T(offs), T(idx)
+    radii = (T(rin), T(rout), T(rs))
+    rnb = T(np.full(n, 1.0))
+    rgrp = T(np.full(n, 0.4))
+
+    def chain(ctx):
+        f_off, f_idx = pt.petar_nb_filter(ctx, pos, vel, mass, rnb, 1.5, doffs, didx)
+        return [f_off, f_idx, *pt.petar_clusters(ctx, f_off, f_idx),
+                *pt.petar_groups(ctx, pos, vel, mass, rgrp, 0.5, doffs, didx)]
+
+    def step(ctx):
+        pt.petar_tree_build(ctx, pos, mass, 0.5, 8)
+        return list(pt.petar_force_long(ctx, 64, *radii))
+
+    free = pt.petar_create(0)
+    want_step = step(free)
+    step_bytes = pt.petar_get_stats(free)["workspace_bytes"]
+    want_chain = chain(free)
+    assert 0 < want_chain[1].numel() < idx.size
+    pt.petar_destroy(free)
+
+    def same(got, want):
+        return len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+
+    ctx = pt.petar_create(0)
+    pt.petar_set_params(ctx, workspace_cap=85 * n)
+    for _ in range(2):
+        assert same(chain(ctx), want_chain)
+    assert pt.petar_get_stats(ctx)["workspace_bytes"] <= 85 * n
+    pt.petar_destroy(ctx)
+    for order in ((chain, step, chain), (step, chain, step)):
+        ctx = pt.petar_create(0)
+        pt.petar_set_params(ctx, workspace_cap=85 * n + step_bytes)
+        for call in order:
+            assert same(call(ctx), want_chain if call is chain else want_step)
+        pt.petar_destroy(ctx)
+
+
