@@ -431,7 +431,7 @@ petar_status filter_impl(petar_ctx *ctx, FilterArgs a, int64_t *out_offsets, int
     const int64_t n = a.n;
     hipStream_t s = ctx->stream;
     const bool own = out_idx == nullptr;
-    TRY(ensure(ctx, ctx->cl_status, 8));
+    TRY(ensure(ctx, ctx->cl_status, sizeof(FilterFlags)));
     TRY(ensure(ctx, ctx->cl_counts, (size_t)(n + 1) * 4));
     TRY(ensure(ctx, ctx->scan_ws, (size_t)scan_ws_elems(n + 1) * 8));
     // first guesses: 16 candidates a star, 4 of them kept. Under a cap none: what
@@ -442,7 +442,7 @@ petar_status filter_impl(petar_ctx *ctx, FilterArgs a, int64_t *out_offsets, int
         if (own) (void)try_grow(ctx, ctx->grp_idx, (size_t)n * 16);
     }
     const size_t rec_bytes = (size_t)n * (size_t)filter_rec_doubles(a.mode) * 8;
-    int32_t *bad = ptr<int32_t>(ctx->cl_status), *csr_bad = bad + 1;
+    FilterFlags *fl = ptr<FilterFlags>(ctx->cl_status);
     while (true) {
         // records where there is room for them: they only save time, and give
         // way to whatever is needed later (see give_way)
@@ -453,14 +453,14 @@ petar_status filter_impl(petar_ctx *ctx, FilterArgs a, int64_t *out_offsets, int
             capacity = (int64_t)(ctx->grp_idx.cap / 4);
         }
         const int64_t mask_cap = (int64_t)(ctx->cl_masks.cap / 8);
-        fill_i64(ptr<int64_t>(ctx->cl_status), 0, 1, s);
-        launch_check_csr(a.offsets, n, csr_bad, s);
+        fill_i64(ptr<int64_t>(ctx->cl_status), 0, sizeof(FilterFlags) / 8, s);
+        launch_check_csr(a.offsets, n, &fl->csr_bad, s);
         launch_filter(a, rec, ptr<uint64_t>(ctx->cl_masks), mask_cap,
-                      ptr<uint32_t>(ctx->cl_counts), bad, csr_bad, s);
+                      ptr<uint32_t>(ctx->cl_counts), fl, s);
         scan_u32_to_i64(ptr<uint32_t>(ctx->cl_counts), out_offsets, n,
-                        ptr<int64_t>(ctx->scan_ws), s);
-        launch_filter_write(a, ptr<uint64_t>(ctx->cl_masks), mask_cap, out_offsets, out_idx,
-                            capacity, bad, csr_bad, ctx->scalar_dev, s);
+                        ptr<int64_t>(ctx->scan_ws), s, &fl->skip);
+        launch_filter_write(a, ptr<uint64_t>(ctx->cl_masks), out_offsets, out_idx, capacity, fl,
+                            ctx->scalar_dev, s);
         HIP_TRY(ctx, hipGetLastError());
         HIP_TRY(ctx, hipStreamSynchronize(s));
         const int64_t kept = ctx->host_scalar[0], n_cand = ctx->host_scalar[1],

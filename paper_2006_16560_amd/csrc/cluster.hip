@@ -153,17 +153,19 @@ __global__ __launch_bounds__(kThreads) void k_filter_pack(FilterArgs a, double4 
 // Decision of every candidate entry: its bit in masks (one word per chunk of
 // 64 entries, the chunks of row block b starting at word b + offsets[64 b] /
 // 64) and the kept entries per row. An index outside [0, n) raises *bad.
-// Nothing is done when the CSR check failed or the words do not fit. kRec:
-// from the records of k_filter_pack, else from the arrays.
+// When the CSR check failed or the words do not fit, flags->skip is all that is
+// written. kRec: from the records of k_filter_pack, else from the arrays.
 template <int MODE, bool kRec>
 __global__ __launch_bounds__(kThreads) void k_filter_test(FilterArgs a, const double4 *rec,
                                                           uint64_t *masks, int64_t mask_cap,
-                                                          uint32_t *counts, int32_t *bad,
-                                                          const int32_t *csr_bad) {
+                                                          uint32_t *counts, FilterFlags *flags) {
     __shared__ RowLds lds[kThreads / kWave];
     __shared__ uint32_t kept[kThreads / kWave][kWave];
     const int64_t n = a.n;
-    if (*csr_bad || filter_words(n, a.offsets[n]) > mask_cap) return;
+    if (flags->csr_bad || filter_words(n, a.offsets[n]) > mask_cap) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) flags->skip = 1;
+        return;
+    }
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int64_t nblk = (n + kWave - 1) / kWave;
     auto point = [&](int64_t i) {
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void k_filter_test(FilterArgs a, const do
             if (e < rows.e1) {
                 const int64_t i = rows.r0 + row, j = a.idx[e];
                 if (j < 0 || j >= n) {
-                    atomicOr(bad, 1);
+                    atomicOr(&flags->bad, 1);
                 } else {
                     const double4 pi = point(i), pj = point(j);
                     if constexpr (MODE == 1) {
@@ -213,18 +215,18 @@ __global__ __launch_bounds__(kThreads) void k_filter_test(FilterArgs a, const do
 // the words the host reads: host[0] = kept entries, host[1] = candidates,
 // host[2] = bad index, bad CSR.
 __global__ __launch_bounds__(kThreads) void k_filter_write(FilterArgs a, const uint64_t *masks,
-                                                           int64_t mask_cap,
                                                            const int64_t *out_offsets,
                                                            int32_t *out_idx, int64_t capacity,
-                                                           const int32_t *bad,
-                                                           const int32_t *csr_bad, int64_t *host) {
+                                                           const FilterFlags *flags,
+                                                           int64_t *host) {
     const int64_t n = a.n;
+    const FilterFlags f = *flags;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        host[0] = out_offsets[n];
-        host[1] = *csr_bad ? 0 : a.offsets[n];
-        host[2] = (*bad ? 1 : 0) | (*csr_bad ? 2 : 0);
+        host[0] = f.skip ? 0 : out_offsets[n];
+        host[1] = f.csr_bad ? 0 : a.offsets[n];
+        host[2] = (f.bad ? 1 : 0) | (f.csr_bad ? 2 : 0);
     }
-    if (*csr_bad || filter_words(n, a.offsets[n]) > mask_cap || out_offsets[n] > capacity) return;
+    if (f.skip || out_offsets[n] > capacity) return;
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int64_t nblk = (n + kWave - 1) / kWave;
     for (int64_t blk = (int64_t)blockIdx.x * (kThreads / kWave) + w; blk < nblk;
@@ -470,14 +472,14 @@ void launch_check_csr(const int64_t *offsets, int64_t n, int32_t *bad, hipStream
 }
 
 void launch_filter(const FilterArgs &a, double *rec, uint64_t *masks, int64_t mask_cap,
-                   uint32_t *counts, int32_t *bad, const int32_t *csr_bad, hipStream_t s) {
+                   uint32_t *counts, FilterFlags *flags, hipStream_t s) {
     const dim3 g(row_grid(a.n)), b(kThreads);
     double4 *r = reinterpret_cast<double4 *>(rec);
     if (rec)
         hipLaunchKernelGGL(k_filter_pack, dim3(grid_for(a.n, kThreads, 8192)), b, 0, s, a, r);
 #define TEST(MODE, REC)                                                                        \
     hipLaunchKernelGGL((k_filter_test<MODE, REC>), g, b, 0, s, a, (const double4 *)r, masks,   \
-                       mask_cap, counts, bad, csr_bad)
+                       mask_cap, counts, flags)
     if (a.mode == 1) {
         if (rec)
             TEST(1, true);
@@ -492,12 +494,11 @@ void launch_filter(const FilterArgs &a, double *rec, uint64_t *masks, int64_t ma
 #undef TEST
 }
 
-void launch_filter_write(const FilterArgs &a, const uint64_t *masks, int64_t mask_cap,
-                         const int64_t *out_offsets, int32_t *out_idx, int64_t capacity,
-                         const int32_t *bad, const int32_t *csr_bad, int64_t *host,
-                         hipStream_t s) {
+void launch_filter_write(const FilterArgs &a, const uint64_t *masks, const int64_t *out_offsets,
+                         int32_t *out_idx, int64_t capacity, const FilterFlags *flags,
+                         int64_t *host, hipStream_t s) {
     hipLaunchKernelGGL(k_filter_write, dim3(row_grid(a.n)), dim3(kThreads), 0, s, a, masks,
-                       mask_cap, out_offsets, out_idx, capacity, bad, csr_bad, host);
+                       out_offsets, out_idx, capacity, flags, host);
 }
 
 void launch_components(const int64_t *offsets, const int32_t *idx, int64_t n, int32_t *parent,

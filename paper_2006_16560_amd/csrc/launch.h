@@ -12,9 +12,11 @@ namespace petar {
 
 // ---------------------------------------------------------------- scan.hip
 // Exclusive prefix sum of n counts into out[0..n] (out[n] = total).
-// ws must hold scan_ws_elems(n) int64 values.
+// ws must hold scan_ws_elems(n) int64 values. Where *skip (device) is set, out
+// is left alone.
 int64_t scan_ws_elems(int64_t n);
-void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s);
+void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s,
+                     const int32_t *skip = nullptr);
 // The same, and the counts are 0 afterwards.
 void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s);
 void scan_u32_to_u32(const uint32_t *in, uint32_t *out, int64_t n, int64_t *ws, hipStream_t s);
@@ -245,16 +247,20 @@ __host__ __device__ inline int64_t filter_words(int64_t n, int64_t n_cand) {
 // Doubles per star in the records of the test (rec, or null: the arrays are
 // read instead).
 inline int64_t filter_rec_doubles(int mode) { return mode == 1 ? 4 : 8; }
-// Decisions as bits (masks, mask_cap words) and kept entries per row; then
-// the kept entries in place, with the words host (pinned) = kept entries,
-// candidates, (bad index) | (bad CSR) << 1. Neither does anything when
-// *csr_bad or when the decisions need more than mask_cap words.
+// Words of a filter call on the device, zeroed by the caller: an index outside
+// [0, n), a CSR that fails the check, and whether the passes must not run: the
+// latter, or decisions that need more than mask_cap words.
+struct FilterFlags {
+    int32_t bad, csr_bad, skip, pad;
+};
+// Decisions as bits (masks, mask_cap words) and kept entries per row, or
+// flags->skip; then (unless that is set) the kept entries in place, with the
+// words host (pinned) = kept entries, candidates, (bad index) | (bad CSR) << 1.
 void launch_filter(const FilterArgs &a, double *rec, uint64_t *masks, int64_t mask_cap,
-                   uint32_t *counts, int32_t *bad, const int32_t *csr_bad, hipStream_t s);
-void launch_filter_write(const FilterArgs &a, const uint64_t *masks, int64_t mask_cap,
-                         const int64_t *out_offsets, int32_t *out_idx, int64_t capacity,
-                         const int32_t *bad, const int32_t *csr_bad, int64_t *host,
-                         hipStream_t s);
+                   uint32_t *counts, FilterFlags *flags, hipStream_t s);
+void launch_filter_write(const FilterArgs &a, const uint64_t *masks, const int64_t *out_offsets,
+                         int32_t *out_idx, int64_t capacity, const FilterFlags *flags,
+                         int64_t *host, hipStream_t s);
 // Components of a neighbour CSR (pairs taken both ways): label[i] =
 // smallest index of i's component, is_root[i] = (label[i] == i); parent is
 // scratch [n]; *bad |= an index outside [0, n). Nothing runs when *csr_bad.

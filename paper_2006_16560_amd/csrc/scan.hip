@@ -92,7 +92,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_totals(int64_t *bsum, int
 template <typename In, typename Out, typename Map, bool kSelf, bool kClear>
 __global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, int64_t n,
                                                              const int64_t *bsum, int64_t nb,
-                                                             int64_t *second) {
+                                                             int64_t *second,
+                                                             const int32_t *skip) {
+    if (skip && *skip) return;
     int64_t before = 0;
     if constexpr (kSelf) {
         int64_t part = 0;
@@ -129,8 +131,9 @@ __global__ __launch_bounds__(kScanThreads) void k_block_scan(In *in, Out *out, i
 // The whole scan by one block, kOneThreads * Items counts at a time.
 template <typename In, typename Out, typename Map, bool kClear>
 __global__ __launch_bounds__(kOneThreads) void k_scan_one(In *in, Out *out, int64_t n,
-                                                          int64_t *second) {
+                                                          int64_t *second, const int32_t *skip) {
     constexpr int Items = 4;
+    if (skip && *skip) return;
     int64_t carry = 0;
     for (int64_t c = 0; c < n; c += (int64_t)kOneThreads * Items) {
         const int64_t base = c + (int64_t)threadIdx.x * Items;
@@ -181,24 +184,24 @@ __global__ void k_words_out(const int64_t *words, int n, int64_t *host) {
 
 template <typename In, typename Out, typename Map, bool kClear>
 void scan_impl(In *in, Out *out, int64_t n, int64_t *ws, hipStream_t s,
-               int64_t *second = nullptr) {
+               int64_t *second = nullptr, const int32_t *skip = nullptr) {
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (nb < 1) nb = 1;
     if (nb <= kOneBlockTiles) {
         hipLaunchKernelGGL((k_scan_one<In, Out, Map, kClear>), dim3(1), dim3(kOneThreads), 0, s,
-                           in, out, n, second);
+                           in, out, n, second, skip);
         return;
     }
     const dim3 g((unsigned)nb), b(kScanThreads);
     hipLaunchKernelGGL((k_block_totals<In, Map>), g, b, 0, s, (const In *)in, n, ws);
     if (nb <= kSelfTotals) {
         hipLaunchKernelGGL((k_block_scan<In, Out, Map, true, kClear>), g, b, 0, s, in, out, n,
-                           (const int64_t *)ws, nb, second);
+                           (const int64_t *)ws, nb, second, skip);
         return;
     }
     hipLaunchKernelGGL(k_scan_totals, dim3(1), b, 0, s, ws, nb);
     hipLaunchKernelGGL((k_block_scan<In, Out, Map, false, kClear>), g, b, 0, s, in, out, n,
-                       (const int64_t *)ws, nb, second);
+                       (const int64_t *)ws, nb, second, skip);
 }
 
 template <typename T>
@@ -213,8 +216,10 @@ void fill_impl(T *p, T v, int64_t n, hipStream_t s) {
 
 int64_t scan_ws_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
 
-void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
-    scan_impl<uint32_t, int64_t, Plain, false>(const_cast<uint32_t *>(in), out, n, ws, s);
+void scan_u32_to_i64(const uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s,
+                     const int32_t *skip) {
+    scan_impl<uint32_t, int64_t, Plain, false>(const_cast<uint32_t *>(in), out, n, ws, s, nullptr,
+                                               skip);
 }
 void scan_u32_to_i64_clear(uint32_t *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
     scan_impl<uint32_t, int64_t, Plain, true>(in, out, n, ws, s);
