@@ -1055,7 +1055,8 @@ void enqueue_nb(petar_ctx *ctx, petar_nblist *nb, hipStream_t s, bool timed, NbR
     int64_t *row_off = ptr<int64_t>(ctx->nbrowoff);
     int32_t *rows = ptr<int32_t>(ctx->nbrows);
     int64_t *ws = ptr<int64_t>(ctx->scan_ws);
-    if (timed) (void)hipEventRecord(ctx->ev[6], s);
+    // a redo belongs to the stage that the first passes began
+    if (timed && mode == kBounds) (void)hipEventRecord(ctx->ev[6], s);
     if (mode != kBounds) fill_u32(queue + 8, 0, 8, s);
     if (mode != kBounds) fill_u32(cnt, 0, n + 1, s);
     if (mode == kExact) {
@@ -1176,6 +1177,8 @@ petar_status finish_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, boo
         }
         if (outgrown || walk) {
             enqueue_nb(ctx, a.nb, s, timed, exact ? kExact : kRedo, walk);
+            // the call's device time ends here (a replay is timed as a whole)
+            HIP_TRY(ctx, hipEventRecord(ctx->ev[timed ? 3 : 1], s));
             HIP_TRY(ctx, hipGetLastError());
             HIP_TRY(ctx, hipStreamSynchronize(s));
         }

@@ -1897,3 +1897,61 @@ def test_filter_leaves_offsets_on_bad_csr(pt, ctx, orc):
             ctypes.c_void_p(dbad.data_ptr()), ctypes.c_void_p(didx.data_ptr()), ctypes.byref(nb))
         assert st == pt.PETAR_E_INVALID
         assert bool((out_off == -7).all()) and bool((out_idx == -7).all())
+
+
+def test_stage_times_cover_redone_lists(pt, orc):
+    """When the near-leaf hand-over overflows, the walk that replaces it and
+    the passes behind it are part of the call's device times: ms_nb lies inside
+    ms_force behind the force kernel, and ms_graph of a replay covers them (the
+    device time around the call exceeds it by far less than those passes
+    take, 0.7 ms here). The overflow itself shows in the larger hand-over
+    buffers of the call that follows."""
+    n = 20000
+    c = workloads.make_cluster(n, 43, imf=True)
+    rin, rout = np.full(n, 0.001), np.full(n, 0.01)
+    few, many = np.full(n, 0.01), np.full(n, 0.2)
+    o_ref, i_ref = orc.neighbours(c.pos, many)
+    need = int(o_ref[-1])
+    dpos, dmass, drin, drout, drs = T(c.pos), T(c.mass), T(rin), T(rout), T(many)
+    ctx = pt.petar_create(0)
+    pt.petar_set_params(ctx, i_per_lane=2)
+    stats = []
+    for _ in range(2):
+        pt.petar_tree_build(ctx, dpos, dmass, 0.5, 8)
+        _, _, (o, i) = pt.petar_force_long(ctx, 64, drin, drout, drs, nb_capacity=need)
+        assert np.array_equal(o.cpu().numpy(), o_ref) and np.array_equal(i.cpu().numpy(), i_ref)
+        stats.append(pt.petar_get_stats(ctx))
+    assert stats[1]["workspace_bytes"] > stats[0]["workspace_bytes"]
+    for st in stats:
+        assert st["ms_force"] >= st["ms_force_kernel"] + st["ms_nb"] - 1e-3
+    redone = stats[0]["ms_nb"]
+    pt.petar_destroy(ctx)
+
+    ctx = pt.petar_create(0)
+    pt.petar_set_params(ctx, i_per_lane=2)
+    acc = torch.empty((3, n), dtype=torch.float64, device="cuda:0")
+    pot = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    nbo = torch.empty(n + 1, dtype=torch.int64, device="cuda:0")
+    nbi = torch.empty(need, dtype=torch.int32, device="cuda:0")
+    drs.copy_(T(few))
+    ws = []
+    for it in range(5):
+        if it == 3:  # same buffers: this replay overflows
+            drs.copy_(T(many))
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda.synchronize()
+        e0.record()
+        tot = pt.petar_step_graph(ctx, dpos, dmass, 0.5, 8, 64, drin, drout, drs, acc, pot,
+                                  nb=(nbo, nbi))
+        e1.record()
+        torch.cuda.synchronize()
+        st = pt.petar_get_stats(ctx)
+        ws.append(st["workspace_bytes"])
+        if it in (1, 2, 3):
+            assert st["ms_graph"] > 0.0
+            assert e0.elapsed_time(e1) - st["ms_graph"] < 0.5 * redone
+        if it >= 3:
+            assert tot == need and np.array_equal(nbo.cpu().numpy(), o_ref)
+            assert np.array_equal(nbi.cpu().numpy(), i_ref)
+    assert ws[4] > ws[2]
+    pt.petar_destroy(ctx)
