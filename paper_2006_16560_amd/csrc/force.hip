@@ -87,9 +87,9 @@ __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x);
 // FP64 reciprocal square root and reciprocal from the hardware's estimates
 // (about 24 bits) and a third-order, respectively two second-order Newton
 // corrections with exact residuals. Where the residual is not a number (0,
-// infinity, NaN) the estimate is the result. Measured against 80-bit results
-// over the whole exponent range: at most 0.5005 and 0.5000 ulp (1.0 /
-// sqrt(x): 1.49), at about a quarter of the instructions.
+// infinity, NaN) the estimate is the result. Within 0.5005 and 0.5001 ulp of
+// the exact results for arguments from 2^-980 to 2^980 and 2^-520 to 2^1000
+// (1.0 / sqrt(x): 1.49), at about a quarter of the instructions.
 __device__ __forceinline__ double rsq(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double h = x * y, hl = fma(x, y, -h);

@@ -1955,3 +1955,61 @@ def test_stage_times_cover_redone_lists(pt, orc):
             assert np.array_equal(nbi.cpu().numpy(), i_ref)
     assert ws[4] > ws[2]
     pt.petar_destroy(ctx)
+
+
+def test_fp64_reciprocals_to_the_half_ulp(pt):
+    """The FP64 mode's reciprocal square root and reciprocal, each alone in a
+    potential, against exact integer arithmetic: pairs (a batch of two-star
+    systems) at separations whose squares are exact, 2^-490 to 2^490, with the
+    changeover far inside (potential -1/r), and pairs far inside r_in
+    (potential -2/(r_in + r_out)) for sums from 2^-520 to 2^1000. Bounds: the
+    half ulp of a correctly rounded result and 0.0005 (third-order correction
+    of the hardware's estimate) or 0.0001 (two second-order ones)."""
+    from fractions import Fraction
+    from math import frexp, isqrt, ldexp
+    rng = np.random.default_rng(49)
+    ctx = pt.petar_create(0)
+    pt.petar_set_params(ctx, precision=pt.PETAR_FP64)
+    n_sys = 512
+    off = [2 * s for s in range(n_sys + 1)]
+
+    def potentials(dx, dy, rin, rout):
+        pos = np.zeros((3, 2 * n_sys))
+        pos[0, 1::2], pos[1, 1::2] = dx, dy
+        rin, rout = np.repeat(rin, 2), np.repeat(rout, 2)
+        pt.petar_batch_build(ctx, off, T(pos), T(np.ones(2 * n_sys)), 0.5, 8)
+        _, pot = pt.petar_force_long(ctx, 64, T(rin), T(rout), T(rout))
+        pot = pot.cpu().numpy()
+        assert np.array_equal(pot[0::2], pot[1::2])  # of both stars
+        return -pot[0::2]
+
+    def ulps(got, num, bits):
+        """|got - num / 2^bits| in units of the last place of got."""
+        ulp = Fraction(2) ** (frexp(got)[1] - 53)
+        return float(abs(Fraction(got) - Fraction(num) / Fraction(2) ** bits) / ulp)
+
+    rsq_worst = rcp_worst = 0.0
+    for _ in range(4):
+        i, j = (rng.integers(1, 1 << 26, n_sys) for _ in range(2))
+        e = rng.integers(-516, 465, n_sys)
+        e[:2] = -516, 464
+        dx, dy = np.ldexp(i.astype(np.float64), e), np.ldexp(j.astype(np.float64), e)
+        r = np.hypot(dx, dy)
+        got = potentials(dx, dy, np.zeros(n_sys), r * 2.0 ** -30)
+        for g, a, b, x in zip(got, i.tolist(), j.tolist(), e.tolist()):
+            s = isqrt((a * a + b * b) << 300)  # 2^150 sqrt(m)
+            rsq_worst = max(rsq_worst, ulps(ldexp(g, x), (1 << 330) // s, 180))
+        x = rng.integers(-520, 1000, n_sys)
+        x[:2] = -520, 999
+        rin, rout = np.ldexp(rng.uniform(0.25, 0.5, n_sys), x), np.ldexp(
+            rng.uniform(0.5, 0.99, n_sys), x)
+        total = rin + rout
+        got = potentials(np.minimum(rin * 2.0 ** -40, 2.0 ** 400), np.zeros(n_sys), rin, rout)
+        for g, t in zip(got, total.tolist()):
+            m, ex = frexp(t)
+            rcp_worst = max(rcp_worst, ulps(ldexp(0.5 * g, ex),
+                                            (1 << 253) // int(ldexp(m, 53)), 200))
+    pt.petar_destroy(ctx)
+    print("rsq %.5f ulp, rcp %.5f ulp" % (rsq_worst, rcp_worst))
+    assert rsq_worst <= 0.5005
+    assert rcp_worst <= 0.5001
