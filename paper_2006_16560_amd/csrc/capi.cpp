@@ -1133,6 +1133,7 @@ void enqueue_force(petar_ctx *ctx, const ForceArgs &a, hipStream_t s, bool timed
     f.precision = prec;
     f.ipl = ipl;
     f.group_size = a.group_size;
+    f.leaf_size = ctx->leaf_size;
     f.cus = ctx->cus;
     if (timed) (void)hipEventRecord(ctx->ev[4], s);
     launch_force(f, fw, s);

@@ -16,6 +16,8 @@
 // at most 64 sources is summed in FP32 and the tile partials are accumulated
 // in FP64 (two instructions per component and tile; a Neumaier-compensated
 // FP32 sum takes seven).
+#include <algorithm>
+
 #include "launch.h"
 #include "walk.h"
 
@@ -1490,24 +1492,41 @@ void launch_team(const ForceLaunch &f, hipStream_t s) {
 // launch takes no less than its slowest group, 0.1 to 0.5 ms, and fills the
 // chip only with some ten groups per resident wave. Teams cut that time and
 // pay for it with the walker's idle lanes and the hand-over of the tiles
-// (4.5% more VALU instructions at a million stars). The lines lie by the
-// groups to be had, about 3.4 n / group_size on clustered particles:
-// kernel times, mixed, two targets per lane, leaf 8 (1m: 4), theta 0.5, ms,
+// (4.9% more VALU instructions at a million stars). The lines lie by the
+// groups to be had, about 3.4 n / group_size on clustered particles. Kernel
+// times, two targets per lane, leaf 8, theta 0.5, ms:
 //   n (group 64)   1k     4k     16k    64k    200k   500k   1m     2m
-//   one wave       0.104  0.207  0.315  0.514  1.01   2.05   4.10   7.59
-//   teams of 4     0.054  0.092  0.153  0.306  0.806  1.92   3.93   8.28
-//   teams of 8     0.047  0.061  0.112  0.302  0.938  2.14   4.63   9.65
-//   teams of 16    0.039  0.050  0.160  0.559
-// (Taken before the large groups were listed first: since then the kernel in
-// use takes 0.093 at 16k, 0.266 at 64k, 0.758 at 200k and 1.88 at 500k; teams
-// of 8 take 0.292 at 64k and 0.441 at 100k, where teams of 4 take 0.398.)
+//   one wave       0.122  0.332  0.517  0.522  0.758  1.816  3.589  7.039
+//   teams of 4     0.055  0.124  0.189  0.274  0.680  1.761  3.806  7.451
+//   teams of 8     0.044  0.083  0.128  0.276  0.830  2.113
+//   teams of 16    0.034  0.073  0.140  0.546
+//   FP64, one wave 0.144  0.435  0.680  0.698  1.415  3.555
+//   teams of 4     0.080  0.189  0.294  0.485  1.427  3.675
+// The line above which one wave is better lies lower for smaller groups: they
+// have fewer tiles for a team to share, and their times differ less, so that a
+// launch of single waves ends together. n / group_size where the two are even
+// (leaf 4 to 16, one or two targets per lane):
+//   group          8      12     16     24     32     48     64     96     192
+//   mixed          600    1300   1600   2300   3000   4500   9000   12000  above 7300
+//   FP64           1200   1600   2000   2200   2900   3100   2800   4300   6000
+// (At n / group_size of 12500, teams of 4 took 1.4 times as long at group 8,
+// 1.25 times at 16.) A leaf larger than group_size is a group as it is. With four
+// targets per lane a team's waves pass their register bounds (31 to 121 VGPRs
+// spilled) and none are built: teams of 4 would take what they take with two per
+// lane (64k, group 64: 0.279 and 0.274 ms; one wave, four per lane, 0.484).
+inline int64_t team_line(const ForceLaunch &f, bool mixed) {
+    const int64_t group = std::max(f.group_size, f.leaf_size);
+    const int64_t most = mixed ? 10000 : std::min<int64_t>(3000 + 8 * group, 10000);
+    return group * std::min(std::max(100 * group, 180 * (group - 14)), most);
+}
+
 template <typename R, int IPL>
 void launch_t(const ForceLaunch &f, int resident_waves, hipStream_t s) {
     if constexpr (IPL <= 2) {
         const int64_t per = f.t.n / f.group_size;
         if (per <= 100) return launch_team<R, IPL, 16>(f, s);
         if (per <= 700) return launch_team<R, IPL, 8>(f, s);
-        if (per <= 20000) return launch_team<R, IPL, 4>(f, s);
+        if (f.t.n <= team_line(f, sizeof(R) == 4)) return launch_team<R, IPL, 4>(f, s);
     }
     const dim3 grid(resident_waves / kWavesPerBlock), block(kThreads);
     if (f.tidx)

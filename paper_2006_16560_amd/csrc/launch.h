@@ -169,7 +169,7 @@ struct ForceLaunch {
     double kick_dt;
     int precision;             // 0 mixed, 1 fp64
     int ipl;                   // 1, 2, 4
-    int group_size;            // of the walk; with n, the number of groups to expect
+    int group_size, leaf_size; // of the walk and tree; with n, the number of groups to expect
     int cus;                   // compute units of the device
     // optional target subset: tpos[k] = targets before Morton position k
     // ([n + 1]), tidx = their Morton positions; null: every particle

@@ -2013,3 +2013,24 @@ def test_fp64_reciprocals_to_the_half_ulp(pt):
     print("rsq %.5f ulp, rcp %.5f ulp" % (rsq_worst, rcp_worst))
     assert rsq_worst <= 0.5005
     assert rcp_worst <= 0.5001
+
+
+@pytest.mark.parametrize("n,group,leaf", [(32400, 18, 8), (32401, 18, 8),   # 1800 times 18
+                                          (32400, 2, 18), (32401, 2, 18)])  # leaves of 18
+def test_force_at_the_last_team_line(pt, ctx, orc, n, group, leaf):
+    """On both sides of the line between teams of four waves and one wave per
+    group, which goes by the larger of group and leaf size: forces, counts and
+    lists of two targets per lane (teams up to the line) equal those of four
+    (one wave per group) bit for bit in both precisions; the tree's groups and
+    the lists are the oracle's."""
+    c, rin, rout, rs = cluster_with_radii(orc, n, n, bf=0.3)
+    o_ref, i_ref = orc.neighbours(c.pos, rs)
+    for prec in (pt.PETAR_FP64, pt.PETAR_MIXED):
+        two, four = (run(pt, ctx, c.pos, c.mass, rin, rout, rs, 0.5, leaf, group, prec,
+                         nb_cap=int(o_ref[-1]), ipl=ipl, counts=True) for ipl in (2, 4))
+        for a, b in zip(two[:2] + [two[3]], four[:2] + [four[3]]):
+            assert np.array_equal(a, b)
+        for offs, idx in (two[2], four[2]):
+            assert np.array_equal(offs, o_ref) and np.array_equal(idx, i_ref)
+        assert pt.petar_get_stats(ctx)["n_groups"] == \
+            orc.tree_info(c.pos, c.mass, leaf, group)["n_groups"]
