@@ -1504,20 +1504,22 @@ void launch_team(const ForceLaunch &f, hipStream_t s) {
 //   teams of 4     0.080  0.189  0.294  0.485  1.427  3.675
 // The line above which one wave is better lies lower for smaller groups: they
 // have fewer tiles for a team to share, and their times differ less, so that a
-// launch of single waves ends together. n / group_size where the two are even
-// (leaf 4 to 16, one or two targets per lane):
+// launch of single waves ends together. n / group_size where the two are even at
+// theta 0.5 (leaf 4 to 16, one or two targets per lane):
 //   group          8      12     16     24     32     48     64     96     192
 //   mixed          600    1300   1600   2300   3000   4500   9000   12000  above 7300
 //   FP64           1200   1600   2000   2200   2900   3100   2800   4300   6000
 // (At n / group_size of 12500, teams of 4 took 1.4 times as long at group 8,
-// 1.25 times at 16.) A leaf larger than group_size is a group as it is. With four
-// targets per lane a team's waves pass their register bounds (31 to 121 VGPRs
-// spilled) and none are built: teams of 4 would take what they take with two per
-// lane (64k, group 64: 0.279 and 0.274 ms; one wave, four per lane, 0.484).
-inline int64_t team_line(const ForceLaunch &f, bool mixed) {
+// 1.25 times at 16; over theta 0.3 to 0.8, 0.93 to 1.4 times at 32.) From 64 on
+// it goes either way, as theta and the cells' sizes have it: up to 20000, teams
+// of 4 took 0.88 to 1.2 times as long at 64 and 0.81 to 1.09 times at 128. A leaf
+// larger than group_size is a group as it is. With four targets per
+// lane a team's waves pass their register bounds (31 to 121 VGPRs spilled) and
+// none are built: teams of 4 would take what they take with two per lane (64k,
+// group 64: 0.279 and 0.274 ms; one wave, four per lane, 0.484).
+inline int64_t team_line(const ForceLaunch &f) {
     const int64_t group = std::max(f.group_size, f.leaf_size);
-    const int64_t most = mixed ? 10000 : std::min<int64_t>(3000 + 8 * group, 10000);
-    return group * std::min(std::max(100 * group, 180 * (group - 14)), most);
+    return group * (group <= 32 ? 100 * group : std::min<int64_t>(525 * group - 13600, 20000));
 }
 
 template <typename R, int IPL>
@@ -1526,7 +1528,7 @@ void launch_t(const ForceLaunch &f, int resident_waves, hipStream_t s) {
         const int64_t per = f.t.n / f.group_size;
         if (per <= 100) return launch_team<R, IPL, 16>(f, s);
         if (per <= 700) return launch_team<R, IPL, 8>(f, s);
-        if (f.t.n <= team_line(f, sizeof(R) == 4)) return launch_team<R, IPL, 4>(f, s);
+        if (f.t.n <= team_line(f)) return launch_team<R, IPL, 4>(f, s);
     }
     const dim3 grid(resident_waves / kWavesPerBlock), block(kThreads);
     if (f.tidx)
