@@ -248,27 +248,39 @@ __global__ __launch_bounds__(kThreads) void k_filter_write(FilterArgs a, const u
 // links the larger of two roots under the smaller with a compare-and-swap;
 // after all unions each component is one tree whose root is its smallest
 // index, whatever the order.
-// The pairs are taken in four passes: each star's smallest neighbour (no
-// swap needed), its first, its last, and then all, with the trees flattened
-// in between. A pass reads the roots that the flattening left (a load inside
-// a launch may return an older parent, since the L2 caches of the XCDs are
-// not coherent within it) and goes on from there with loads and swaps at the
-// coherence point. In one pass, every pair inside a percolating cluster
-// climbed from its stars' old roots to the common root with swaps on the
-// same few words, 2.7 ms at a million stars; after the sampling passes
-// nearly all stars of such a cluster have the same root, and their pairs
-// end with one comparison (0.1 ms).
-// rep() follows the pointers and halves the path behind it with plain
-// stores, which only ever replace a non-root's parent by one of its
-// ancestors (used where no swap runs at the same time).
-__device__ __forceinline__ int32_t uf_rep(int32_t *parent, int32_t v) {
-    int32_t cur = parent[v];
-    if (cur == v) return v;
-    int32_t prev = v, next;
-    while (cur > (next = parent[cur])) {
-        parent[prev] = next;
-        prev = cur;
+// The pairs are taken in three passes: each star's smallest neighbour (no
+// swap needed; the start of ECL-CC, Jaiganesh and Burtscher 2018), its first and
+// its last (neighbour sampling as in Afforest, Sutton et al. 2018), and then
+// all, with the trees flattened in between. A pass reads the roots that the
+// flattening left (a load inside a launch may return an older parent, since the
+// L2 caches of the XCDs are not coherent within it) and goes on from there with
+// loads and swaps at the coherence point. In one pass, every pair inside a
+// percolating cluster climbed from its stars' old roots to the common root with
+// swaps on the same few words, 2.7 ms at a million stars; after the sampling
+// nearly all stars of such a cluster have the same root, and their pairs end
+// with one comparison (0.1 ms).
+// uf_root gives the root of v and leaves parent[v] there (where no swap runs at
+// the same time). A chain is followed for kShallow steps; what is longer is
+// shortened by all its stars at once: each star's pointer goes on to its parent's
+// pointer, stored and read at the coherence point, until that is the root. (When
+// each star walked the chain by itself, halving it behind it, three million stars
+// in a row took 1 s, now 0.5 ms.)
+constexpr int kShallow = 16;
+__device__ __forceinline__ int32_t uf_root(int32_t *parent, int32_t v) {
+    const int32_t first = parent[v];
+    int32_t cur = first, next = parent[cur];
+    for (int k = 0; k < kShallow && next != cur; k++) {
         cur = next;
+        next = parent[cur];
+    }
+    if (next == cur) {
+        if (cur != first) parent[v] = cur;
+        return cur;
+    }
+    while (next != cur) {
+        cur = next;
+        __hip_atomic_store(parent + v, cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        next = __hip_atomic_load(parent + cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return cur;
 }
@@ -308,12 +320,17 @@ __global__ __launch_bounds__(kThreads) void k_uf_flatten(int32_t *parent, int64_
     if (*csr_bad) return;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x)
-        parent[v] = uf_rep(parent, (int32_t)v);
+        (void)uf_root(parent, (int32_t)v);
 }
 
-// Joins the trees of a and b, ancestors of two stars (or the stars).
+// Joins the trees of a and b, ancestors of two stars (or the stars). Trees that
+// the pass itself has made deep are halved on the way from kJoinSteps on (a
+// million stars of a lattice, each with its neighbours of larger index only: 0.95
+// ms instead of 1.27); earlier, the stores slow every other climb down (lists of
+// 20 neighbours: 1.45 ms from 8 on, 0.96 from 32 on).
+constexpr int kJoinSteps = 32;
 __device__ __forceinline__ void uf_join(int32_t *parent, int32_t a, int32_t b) {
-    while (a != b) {
+    for (int k = 0; a != b; k++) {
         if (a < b) {
             const int32_t t = a;
             a = b;
@@ -323,22 +340,30 @@ __device__ __forceinline__ void uf_join(int32_t *parent, int32_t a, int32_t b) {
         if (p == a) {
             p = atomicCAS(parent + a, a, b);
             if (p == a) return;
+        } else if (k >= kJoinSteps) {
+            const int32_t q =
+                __hip_atomic_load(parent + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (q != p) {
+                __hip_atomic_store(parent + a, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                p = q;
+            }
         }
         a = p;  // a smaller ancestor of a
     }
 }
 
-// One pair per row: its first entry, or its last.
+// Two pairs per row: its first entry and its last.
 __global__ __launch_bounds__(kThreads) void k_uf_sample(const int64_t *offsets, const int32_t *idx,
-                                                        int64_t n, int32_t *parent, bool last,
+                                                        int64_t n, int32_t *parent,
                                                         const int32_t *csr_bad) {
     if (*csr_bad) return;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x) {
         const int64_t beg = offsets[v], end = offsets[v + 1];
         if (beg == end) continue;
-        const int32_t u = idx[last ? end - 1 : beg];
-        if (u >= 0 && u < n) uf_join(parent, parent[v], parent[u]);
+        const int32_t u = idx[beg], w = idx[end - 1], r = parent[v];
+        if (u >= 0 && u < n) uf_join(parent, r, parent[u]);
+        if (w != u && w >= 0 && w < n) uf_join(parent, r, parent[w]);
     }
 }
 
@@ -373,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void k_uf_label(int32_t *parent, int64_t 
     const bool skip = *csr_bad != 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = skip ? (int32_t)v : uf_rep(parent, (int32_t)v);
+        const int32_t r = skip ? (int32_t)v : uf_root(parent, (int32_t)v);
         label[v] = r;
         is_root[v] = r == (int32_t)v ? 1u : 0u;
     }
@@ -504,13 +529,13 @@ void launch_filter_write(const FilterArgs &a, const uint64_t *masks, const int64
 void launch_components(const int64_t *offsets, const int32_t *idx, int64_t n, int32_t *parent,
                        int32_t *label, uint32_t *is_root, int32_t *bad, const int32_t *csr_bad,
                        hipStream_t s) {
-    const dim3 g(grid_for(n, kThreads, 8192)), b(kThreads);
+    // a thread per star: the stars of smaller indices, which chains lead to, start
+    // first, so that a chain's halving begins at its root
+    const dim3 g(grid_for(n, kThreads, INT32_MAX)), b(kThreads);
     const dim3 gr(row_grid(n));
     hipLaunchKernelGGL(k_uf_init, gr, b, 0, s, offsets, idx, n, parent, csr_bad);
-    for (int last = 0; last < 2; last++) {
-        hipLaunchKernelGGL(k_uf_flatten, g, b, 0, s, parent, n, csr_bad);
-        hipLaunchKernelGGL(k_uf_sample, g, b, 0, s, offsets, idx, n, parent, last != 0, csr_bad);
-    }
+    hipLaunchKernelGGL(k_uf_flatten, g, b, 0, s, parent, n, csr_bad);
+    hipLaunchKernelGGL(k_uf_sample, g, b, 0, s, offsets, idx, n, parent, csr_bad);
     hipLaunchKernelGGL(k_uf_flatten, g, b, 0, s, parent, n, csr_bad);
     hipLaunchKernelGGL(k_uf_union, gr, b, 0, s, offsets, idx, n, parent, bad, csr_bad);
     hipLaunchKernelGGL(k_uf_label, g, b, 0, s, parent, n, label, is_root, csr_bad);

@@ -2034,3 +2034,43 @@ def test_force_at_the_last_team_line(pt, ctx, orc, n, group, leaf):
             assert np.array_equal(offs, o_ref) and np.array_equal(idx, i_ref)
         assert pt.petar_get_stats(ctx)["n_groups"] == \
             orc.tree_info(c.pos, c.mass, leaf, group)["n_groups"]
+
+
+@pytest.mark.parametrize("n", [2, 17, 18, 2000, 70000])
+@pytest.mark.parametrize("shape", ["up", "down", "both", "permuted", "middle", "lattice", "tree",
+                                   "star"])
+def test_clusters_of_long_chains(pt, ctx, orc, shape, n):
+    """Graphs whose unions make long chains of parents: stars in a row (each
+    listing the next, the one before, or both; in the order of the indices or
+    not; in the middle of a row of self entries), a lattice, a binary tree, a
+    star: labels, offsets and members are the oracle's."""
+    rng = np.random.default_rng(n)
+    i = np.arange(n - 1)
+    if shape == "up":
+        a, b = i, i + 1
+    elif shape == "down":
+        a, b = i + 1, i
+    elif shape == "both":
+        a, b = np.concatenate([i, i + 1]), np.concatenate([i + 1, i])
+    elif shape == "permuted":
+        p = rng.permutation(n)
+        a, b = p[:-1], p[1:]
+    elif shape == "middle":
+        a, b = np.repeat(i, 3), np.stack([i, i + 1, i], 1).ravel()
+    elif shape == "lattice":
+        side = int(n ** 0.5)
+        right = i[i % side < side - 1]
+        a = np.concatenate([right, i[i < n - side]])
+        b = np.concatenate([right + 1, i[i < n - side] + side])
+    elif shape == "tree":
+        a, b = i + 1, i // 2
+    else:
+        a, b = np.full(n - 1, n // 2), rng.permutation(n)[:n - 1]
+    order = np.argsort(a, kind="stable")
+    offs = np.zeros(n + 1, dtype=np.int64)
+    offs[1:] = np.cumsum(np.bincount(a, minlength=n))
+    idx = b[order].astype(np.int32)
+    ref = orc.clusters(n, offs, idx)
+    for f in (pt.petar_clusters, pt.petar_clusters_noalloc):
+        for got, want in zip(f(ctx, T(offs), T(idx)), ref):
+            assert np.array_equal(got.cpu().numpy(), want)
