@@ -2074,3 +2074,31 @@ def test_clusters_of_long_chains(pt, ctx, orc, shape, n):
     for f in (pt.petar_clusters, pt.petar_clusters_noalloc):
         for got, want in zip(f(ctx, T(offs), T(idx)), ref):
             assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,k", [(1, 0), (4000, 0), (4000, 999), (4000, 1000), (4001, 1001)])
+def test_filter_with_few_candidates(pt, ctx, orc, n, k):
+    """Up to and from one candidate in four stars, where the filter's test goes
+    over from the arrays to star records: kept lists and groups are the
+    oracle's."""
+    c = workloads.make_cluster(n, 50 + n, imf=True, binary_fraction=0.6 if n > 1 else 0.0)
+    rng = np.random.default_rng(k)
+    rin, rout, rnb = orc.radii(c.mass, 0.3, 0.8, 1.2)
+    i = np.sort(rng.integers(0, n, k))
+    offs = np.zeros(n + 1, dtype=np.int64)
+    offs[1:] = np.cumsum(np.bincount(i, minlength=n))
+    idx = rng.integers(0, n, k).astype(np.int32)
+    args = (T(c.pos), T(c.vel), T(c.mass))
+    f_off, f_idx = pt.petar_nb_filter(ctx, *args, T(rnb), 1.5, T(offs), T(idx))
+    o_ref, i_ref = orc.nb_filter(c.pos, c.vel, c.mass, rnb, 1.5, offs, idx)
+    assert np.array_equal(f_off.cpu().numpy(), o_ref)
+    assert np.array_equal(f_idx.cpu().numpy(), i_ref)
+    assert k == 0 or 0 < i_ref.size < k
+    got = pt.petar_groups(ctx, *args, T(rin), 0.5, T(offs), T(idx))
+    j = idx.astype(np.int64)
+    close = ((c.pos[:, j] - c.pos[:, i]) ** 2).sum(axis=0) < (0.5 * np.maximum(rin[i], rin[j])) ** 2
+    g_off = np.zeros(n + 1, dtype=np.int64)
+    g_off[1:] = np.cumsum(np.bincount(i[close], minlength=n))
+    want = orc.clusters(n, g_off, idx[close])
+    for a, b in zip(got, want):
+        assert np.array_equal(a.cpu().numpy(), b)
